@@ -190,6 +190,7 @@ constexpr int kGroups = 64 / kSlices;                 // groups of a wave
 constexpr int kRows = 1024;   // stencil rows listed at a time
 constexpr int kList = 192;    // particles listed per group: emptied above kList - 64
 constexpr int kTake = kSlices;                        // particles a lane lists per round
+constexpr int kAhead = 4;                             // rows a lane looks up at once
 
 enum ShepardMode { kGather = 0, kCountPairs = 1, kFillPairs = 2 };
 constexpr unsigned long long kMaxPairs = 1ull << 29;   // recorded pairs: at most 6 GiB
@@ -213,11 +214,21 @@ __device__ inline unsigned pairs_before(uint2 c, int s)
 // The support test itself is exact (FP64).
 //
 // The block lists the stencil's rows once (offset, half-length, class) in
-// LDS.  Then a group's lanes look up one row each, and append its particles
-// (at most kTake each per round, in lane order) to the group's list in LDS;
-// from there they go to the lanes in turn, entry j to lane j mod 8, so the
-// lanes are busy alike whatever the rows hold.  Each lane sums its entries in
-// order and the eight sums are added by a butterfly, a fixed order.
+// LDS, those that lie outside the grid for all its centres left out.  A class
+// of fewer particles than its stencil has rows (a few wide kernels, or fewer
+// particles than cells) is taken whole instead, in one part per lane: looking
+// up its rows would cost more than testing its particles (one kernel of
+// 2h = 1.2 boxes among 2^20 particles on 128^3 cells: 62 ms by rows, 0.8 whole;
+// the line was measured at 1000 kernels of 2h = 0.2 boxes, 2000 rows: 2.2 ms
+// whole, 2.9 by rows).
+// Then a group's lanes look up kAhead rows each, their loads under way
+// together, and append the rows' particles (at most kTake each per round, in
+// lane order) to the group's list in LDS; from there they go to the lanes in
+// turn, entry j to lane j mod 8, so the lanes are busy alike whatever the rows
+// hold.  (16384 particles on 128^3 cells, whose rows are nearly all empty: the
+// build takes 1166 us with one row at a time, 961 with four, 934 with six; one
+// particle per cell on 64^3 cells: 290 to 300 with any.)  Each lane sums its
+// entries in order and the eight sums are added by a butterfly, a fixed order.
 //
 // What bounds it: FP64 ALU on large grids (~27 instructions per centre and
 // listed particle, of which ~60% lie in the support), latency on small ones.
@@ -245,7 +256,8 @@ __global__ void __launch_bounds__(kThreads) shepard_gather(start_box box, double
                                                            unsigned *__restrict__ pidx, double *__restrict__ pw,
                                                            double *__restrict__ pden, unsigned *__restrict__ many)
 {
-    __shared__ int2 row_all[kRows];             // (da << 16 | db & 0xffff, half-length << 2 | class)
+    __shared__ int2 row_all[kRows];             // (da << 16 | db & 0xffff, half-length << 2 | class),
+                                                // or (part of a class, -1 - class)
     __shared__ unsigned list_all[kThreads / 64][kGroups][kList];
     __shared__ int wrows[kThreads / 64];
     const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
@@ -255,6 +267,7 @@ __global__ void __launch_bounds__(kThreads) shepard_gather(start_box box, double
     const int64_t n_groups = (int64_t)G * G * GZ;
     // blocks are dealt round-robin to the 8 XCDs: each gets a contiguous part
     // of the grid, whose particles stay in its L2
+    const int log2g = __builtin_ctz((unsigned)G);
     const int nb = (int)gridDim.x, per_xcd = nb / 8;
     int blk = (int)blockIdx.x;
     if (per_xcd > 0 && blk < per_xcd * 8) blk = (blk & 7) * per_xcd + (blk >> 3);
@@ -341,13 +354,22 @@ __global__ void __launch_bounds__(kThreads) shepard_gather(start_box box, double
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
 
-    // all rows of the classes' squares, kRows at a time
-    int first_row[kMaxReachClasses + 1];
+    // the cells of the block's centres: x from A0 to A1, y from B0 to B1
+    const int64_t lin0 = (int64_t)blk * (kThreads / kSlices);
+    const int64_t lin1 = min(lin0 + kThreads / kSlices, n_groups) - 1;
+    const int A0 = (int)(lin0 / ((int64_t)G * GZ)), A1 = (int)(lin1 / ((int64_t)G * GZ));
+    const int B0 = A0 == A1 ? (int)((lin0 / GZ) % G) : 0, B1 = A0 == A1 ? (int)((lin1 / GZ) % G) : G - 1;
+    // all rows of the classes' squares that meet the grid, kRows at a time
+    int first_row[kMaxReachClasses + 1], a_lo[kMaxReachClasses], b_lo[kMaxReachClasses], n_b[kMaxReachClasses];
     first_row[0] = 0;
 #pragma unroll
     for (int k = 0; k < kMaxReachClasses; ++k) {
-        const int d = 2 * cls.R[k] + 1;
-        first_row[k + 1] = first_row[k] + (k < cls.K ? d * d : 0);
+        const int R = cls.R[k];
+        a_lo[k] = max(-R, -A1);
+        b_lo[k] = max(-R, -B1);
+        n_b[k] = min(R, G - 1 - B0) - b_lo[k] + 1;
+        const int n_a = min(R, G - 1 - A0) - a_lo[k] + 1;
+        first_row[k + 1] = first_row[k] + (k < cls.K ? (cls.whole[k] ? kSlices : n_a * n_b[k]) : 0);
     }
     for (int base = 0; base < first_row[kMaxReachClasses]; base += kRows) {
         // 1. the rows that reach the centres, in order
@@ -358,16 +380,26 @@ __global__ void __launch_bounds__(kThreads) shepard_gather(start_box box, double
             bool in = false;
             int2 e = make_int2(0, 0);
             if (r < first_row[kMaxReachClasses]) {
-                int k = 0;
-                while (k + 1 < cls.K && r >= first_row[k + 1]) ++k;
-                const int R = cls.R[k], d = 2 * R + 1, i = r - first_row[k];
-                const int da = i / d - R, db = i % d - R;
-                const float fa = da == 0 ? 0.0f : (float)abs(da) - 0.5f;
-                const float fb = db == 0 ? 0.0f : (float)abs(db) - 0.5f;
-                const float rem = cls.q2[k] - fa * fa - fb * fb;
-                in = rem >= 0.0f;
-                const float rz = fminf(sqrtf(in ? rem : 0.0f) + 0.5f, (float)G);
-                e = make_int2((int)((unsigned)da << 16 | ((unsigned)db & 0xFFFFu)), ((int)rz << 2) | k);
+                int k = 0, i = r, al = a_lo[0], bl = b_lo[0], nb = n_b[0], whole = cls.whole[0];
+                float q2 = cls.q2[0];
+#pragma unroll
+                for (int c = 1; c < kMaxReachClasses; ++c)
+                    if (c < cls.K && r >= first_row[c]) {
+                        k = c, i = r - first_row[c], al = a_lo[c], bl = b_lo[c], nb = n_b[c], whole = cls.whole[c];
+                        q2 = cls.q2[c];
+                    }
+                if (whole) {
+                    in = true;
+                    e = make_int2(i, -1 - k);
+                } else {
+                    const int da = i / nb + al, db = i % nb + bl;
+                    const float fa = da == 0 ? 0.0f : (float)abs(da) - 0.5f;
+                    const float fb = db == 0 ? 0.0f : (float)abs(db) - 0.5f;
+                    const float rem = q2 - fa * fa - fb * fb;
+                    in = rem >= 0.0f;
+                    const float rz = fminf(sqrtf(in ? rem : 0.0f) + 0.5f, (float)G);
+                    e = make_int2((int)((unsigned)da << 16 | ((unsigned)db & 0xFFFFu)), ((int)rz << 2) | k);
+                }
             }
             const uint64_t m = __ballot(in);
             if (lane == 0) wrows[w] = __popcll(m);
@@ -381,33 +413,61 @@ __global__ void __launch_bounds__(kThreads) shepard_gather(start_box box, double
             __syncthreads();
         }
         // 2. their particles
-        unsigned cur = 0, end = 0;
-        int r = sl;
-        while (__any(cur < end || r < rows)) {
-            if (cur == end && r < rows) {
-                const int2 e = row_all[r];
-                r += kSlices;
-                const int a = ia + (e.x >> 16), b = ib + (int)(short)(e.x & 0xFFFF), rz = e.y >> 2;
-                if (live && a >= 0 && a < G && b >= 0 && b < G) {
-                    const int z0 = ic0 - rz < 0 ? 0 : ic0 - rz;
-                    const int z1 = ic0 + nz - 1 + rz >= G ? G - 1 : ic0 + nz - 1 + rz;
-                    const unsigned *const st = start + (e.y & 3) * ncell + ((int64_t)a * G + b) * G;
-                    cur = st[z0];
-                    end = st[z1 + 1];
-                }
+        // a row's first particle and number of particles (32-bit places: at
+        // most 2 classes of 1024^3 cells)
+        auto look_up = [&](const int2 e, unsigned &at, unsigned &num) {
+            at = num = 0;
+            if (e.y < 0) {
+                const unsigned *const st = start + (int64_t)(-1 - e.y) * ncell;
+                const unsigned s0 = st[0], n = st[ncell] - s0;   // (n < 2^20: a stencil's rows at most)
+                at = s0 + n * (unsigned)e.x / kSlices;
+                num = live ? s0 + n * (unsigned)(e.x + 1) / kSlices - at : 0u;
+                return;
             }
-            const int take = (int)min(end - cur, (unsigned)kTake);
-            int incl = take;
+            const unsigned a = (unsigned)(ia + (e.x >> 16)), b = (unsigned)(ib + (int)(short)(e.x & 0xFFFF));
+            if (live && a < (unsigned)G && b < (unsigned)G) {
+                const int rz = e.y >> 2;
+                const unsigned row = ((unsigned)(e.y & 3) * (unsigned)G + a) * (unsigned)G + b;
+                const unsigned *const st = start + (row << log2g);
+                at = st[max(ic0 - rz, 0)];
+                num = st[min(ic0 + nz - 1 + rz, G - 1) + 1] - at;
+            }
+        };
+        for (int r = sl; __any(r < rows); r += kAhead * kSlices) {
+            unsigned cur[kAhead], left[kAhead];
 #pragma unroll
-            for (int o = 1; o < kSlices; o <<= 1) {
-                const int v = __shfl_up(incl, o, kSlices);
-                if (sl >= o) incl += v;
+            for (int u = 0; u < kAhead; ++u) {
+                cur[u] = left[u] = 0;
+                if (r + u * kSlices < rows) look_up(row_all[r + u * kSlices], cur[u], left[u]);
             }
-            unsigned *const to = list + listed + incl - take;
-            for (int i = 0; i < take; ++i) to[i] = cur + (unsigned)i;
-            cur += (unsigned)take;
-            listed += __shfl(incl, kSlices - 1, kSlices);
-            if (__any(listed > kList - kSlices * kTake)) empty_list();
+            for (;;) {
+                unsigned more = 0;
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) more |= left[u];
+                if (!__any(more != 0)) break;
+                unsigned take[kAhead], sum = 0;
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    take[u] = min(left[u], (unsigned)kTake - sum);
+                    sum += take[u];
+                }
+                int incl = (int)sum;
+#pragma unroll
+                for (int o = 1; o < kSlices; o <<= 1) {
+                    const int v = __shfl_up(incl, o, kSlices);
+                    if (sl >= o) incl += v;
+                }
+                unsigned *to = list + listed + incl - sum;
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    for (unsigned i = 0; i < take[u]; ++i) to[i] = cur[u] + i;
+                    to += take[u];
+                    cur[u] += take[u];
+                    left[u] -= take[u];
+                }
+                listed += __shfl(incl, kSlices - 1, kSlices);
+                if (__any(listed > kList - kSlices * kTake)) empty_list();
+            }
         }
     }
     empty_list();
@@ -615,6 +675,9 @@ static ReachClasses choose_classes(const unsigned *hist, int G, int64_t ncell, d
         // stencil arithmetic; it only ever adds cells to the scan
         c.q2[k] = (float)(r * r * (1.0 + 1e-4) + 1e-4);
         c.R[k] = (int)std::min(floor(0.5 + sqrt((double)c.q2[k])), (double)(G - 1));   // no row is further
+        // fewer particles than the stencil has rows inside the grid
+        const double rows = std::min(M_PI * (r + 0.5) * (r + 0.5), (double)G * G);
+        c.whole[k] = pre[last[k] + 1] - pre[k > 0 ? last[k - 1] + 1 : 0] <= rows;
         if (k < 3 && k < K - 1) t[k] = bin[last[k]];
     }
     *top = make_int4(t[0], t[1], t[2], 0);

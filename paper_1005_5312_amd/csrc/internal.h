@@ -153,6 +153,7 @@ struct ReachClasses {
     int K = 1;
     int R[kMaxReachClasses] = {};      // loop half-width in cells
     float q2[kMaxReachClasses] = {};   // (reach / delta)^2 with a small safety margin
+    int whole[kMaxReachClasses] = {};  // 1: its particles are taken whole, without looking up rows
 };
 
 struct GasBins {
