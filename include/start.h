@@ -359,7 +359,7 @@ start_status start_diffuse_equilibrium(start_ctx *ctx, const start_box *box, int
 start_status start_set_graph_replay(start_ctx *ctx, int enable);
 
 /* Whether the equilibrium loops (start_ionization_equilibrium,
- * start_diffuse_equilibrium) record, with their first grid, every (grid
+ * start_diffuse_equilibrium) record, with their second grid, every (grid
  * cell, gas particle) pair inside the kernel support with its weight
  * (12 bytes per pair, ~32 pairs per cell at one particle per cell) and
  * refill the grid from them (default on), or search the stencil at every

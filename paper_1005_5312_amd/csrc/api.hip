@@ -353,11 +353,10 @@ start_status wait_stream(start_ctx *ctx, unsigned long long *word, double *value
 }
 
 // The first grid of an equilibrium loop, from the binned n_HI.  Where more
-// iterations may follow, the (centre, particle) pairs are recorded on the way
-// (the recording fills the grid with the same values, so a stencil search of
-// its own is saved) and the later refills read them; without the memory for
-// them they search the stencil.  The rate call's scratch is taken first, so
-// that the pairs only use what it leaves.
+// iterations may follow, the (centre, particle) pairs are counted on the way;
+// they are recorded with the second grid (second_fill), since many loops end
+// before it.  The rate call's scratch is taken first, so that the pairs only
+// use what it leaves.
 start_status first_fill(start_ctx *ctx, const RateSpec &r, GasBins *bins, Grid *grid, int max_iter)
 {
     Ctx &c = ctx->c;
@@ -365,11 +364,25 @@ start_status first_fill(start_ctx *ctx, const RateSpec &r, GasBins *bins, Grid *
         int tile = 0;
         start_status st = reserve(ctx, &r, 1, &tile);
         if (st) return st;
-        st = record_pairs(&c, bins, grid);
+        st = count_pairs(&c, bins, grid);
+        if (st == START_OK) return st;
+    }
+    fill_grid(&c, *bins, nullptr, grid);
+    return START_OK;
+}
+
+// The second grid, from nhi.  The recording fills it with the same values as a
+// stencil search of its own, and the later refills read the pairs; without the
+// memory for them every refill searches the stencil.
+start_status second_fill(start_ctx *ctx, GasBins *bins, const double *nhi, Grid *grid)
+{
+    Ctx &c = ctx->c;
+    if (bins->counted) {
+        const start_status st = record_pairs(&c, bins, nhi, grid);
         if (st == START_OK) return st;
         if (st != START_ENOMEM) return fail(ctx, st, "grid pair recording failed");
     }
-    fill_grid(&c, *bins, nullptr, grid);
+    fill_grid(&c, *bins, nhi, grid);
     return START_OK;
 }
 
@@ -1134,15 +1147,18 @@ start_status start_ionization_equilibrium(start_ctx *ctx, const start_tree *tree
     r.gamma = gamma_out;
     // The first iteration stages the rate call (tables, target sort); the
     // later ones repeat the same kernels on the same buffers (grid refill,
-    // rate kernels, equilibrium update), replayed from a HIP graph when
-    // graphs are on.
+    // rate kernels, equilibrium update), from the third on replayed from a HIP
+    // graph when graphs are on (the second records the grid's pairs).
     BatchLaunch bl{};
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
-    auto iteration_kernels = [&]() {
-        fill_grid(&c, bins, nhi, &grid);
+    auto rates_and_update = [&]() {
         relaunch_batch(bl, c.stream);
         launch_eq_update(&c, n_gas, n_h, gamma_out, prec, alpha, x_hi, nhi, word);
+    };
+    auto iteration_kernels = [&]() {
+        fill_grid(&c, bins, nhi, &grid);
+        rates_and_update();
     };
     auto drop_graph = [&]() {
         if (gexec) hipGraphExecDestroy(gexec);
@@ -1158,6 +1174,10 @@ start_status start_ionization_equilibrium(start_ctx *ctx, const start_tree *tree
             if (st) return cleanup(st);
             launch_clear_word(&c, word);
             launch_eq_update(&c, n_gas, n_h, gamma_out, prec, alpha, x_hi, nhi, word);
+        } else if (it == 2) {
+            st = second_fill(ctx, &bins, nhi, &grid);
+            if (st) return cleanup(st);
+            rates_and_update();
         } else if (c.graphs) {
             if (!gexec) {
                 hipError_t e = hipStreamBeginCapture(c.stream, hipStreamCaptureModeThreadLocal);
@@ -1305,6 +1325,9 @@ start_status start_diffuse_equilibrium(start_ctx *ctx, const start_box *box, int
         r.gamma = gamma_out;
         if (it == 1) {
             st = first_fill(ctx, r, &bins, &grid, max_iter);
+            if (st) return done(st);
+        } else if (it == 2) {
+            st = second_fill(ctx, &bins, nhi, &grid);
             if (st) return done(st);
         } else {
             fill_grid(&c, bins, nhi, &grid);

@@ -192,7 +192,7 @@ constexpr int kList = 192;    // particles listed per group: emptied above kList
 constexpr int kTake = kSlices;                        // particles a lane lists per round
 constexpr int kAhead = 4;                             // rows a lane looks up at once
 
-enum ShepardMode { kGather = 0, kCountPairs = 1, kFillPairs = 2 };
+enum ShepardMode { kGather = 0, kGatherCount = 1, kFillPairs = 2 };
 constexpr unsigned long long kMaxPairs = 1ull << 29;   // recorded pairs: at most 6 GiB
 
 // Number of pairs of slices 0..s-1 in a cell's eight one-byte counts.
@@ -237,24 +237,21 @@ __device__ inline unsigned pairs_before(uint2 c, int s)
 // the longest run: 195 us on 32^3, 239 on 64^3, 771 on 128^3; now 24, 88 and
 // 555 (alone).
 //
-// kCountPairs counts the (centre, particle) pairs inside the support of each
-// centre and slice; kFillPairs also records them with their weights, slice by
+// kGatherCount also counts the (centre, particle) pairs inside the support of
+// each centre and slice; kFillPairs records them with their weights, slice by
 // slice in summation order, and the weight sums (for refills with new n_HI at
 // the same positions, refill_pairs).  The pairs of 64 consecutive cells are
 // stored interleaved (pair q of the group's cell l at q * 64 + l, the group
 // padded to its longest list), so that a wave refilling those cells reads
 // consecutive addresses at every step.
 template <int MODE>
-__global__ void __launch_bounds__(kThreads) shepard_gather(start_box box, double delta, int G, ReachClasses cls,
-                                                           const unsigned *__restrict__ start,
-                                                           const double4 *__restrict__ pos_h,
-                                                           const double2 *__restrict__ kern,
-                                                           const double *__restrict__ ns, double *val, float *valf,
-                                                           int sx, int sy, uint2 *__restrict__ pslice,
-                                                           unsigned *__restrict__ pcount,
-                                                           const unsigned *__restrict__ pstart,
-                                                           unsigned *__restrict__ pidx, double *__restrict__ pw,
-                                                           double *__restrict__ pden, unsigned *__restrict__ many)
+__global__ void __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(MODE == kFillPairs ? 3 : 4)))
+shepard_gather(start_box box, double delta, int G, ReachClasses cls, const unsigned *__restrict__ start,
+               const double4 *__restrict__ pos_h, const double2 *__restrict__ kern, const double *__restrict__ ns,
+               double *val, float *valf, int sx, int sy, uint2 *__restrict__ pslice, unsigned *__restrict__ pcount,
+               const unsigned *__restrict__ pstart, unsigned *__restrict__ pidx, double *__restrict__ pw,
+               double *__restrict__ pden, unsigned *__restrict__ many)
 {
     __shared__ int2 row_all[kRows];             // (da << 16 | db & 0xffff, half-length << 2 | class),
                                                 // or (part of a class, -1 - class)
@@ -303,10 +300,8 @@ __global__ void __launch_bounds__(kThreads) shepard_gather(start_box box, double
         double nn = 0.0;
         if (sl < listed) {
             pn = pos_h[at];
-            if (MODE != kCountPairs) {
-                kn = kern[at];
-                nn = ns[at];
-            }
+            kn = kern[at];
+            nn = ns[at];
         }
         for (int j = sl; j < listed; j += kSlices) {
             const unsigned s = at;
@@ -316,10 +311,8 @@ __global__ void __launch_bounds__(kThreads) shepard_gather(start_box box, double
             if (j + kSlices < listed) {
                 at = list[j + kSlices];
                 pn = pos_h[at];
-                if (MODE != kCountPairs) {
-                    kn = kern[at];
-                    nn = ns[at];
-                }
+                kn = kern[at];
+                nn = ns[at];
             }
             const double dx = xc - p.x, dy = yc - p.y;
             const double dxy2 = dx * dx + dy * dy, h2 = 4.0 * p.w * p.w;
@@ -331,10 +324,7 @@ __global__ void __launch_bounds__(kThreads) shepard_gather(start_box box, double
                 const double dz = zc[c] - p.z;
                 const double r2 = dxy2 + dz * dz;
                 const bool in = c < nz && r2 < h2;
-                if (MODE == kCountPairs) {
-                    cnt[c] += in ? 1u : 0u;
-                    continue;
-                }
+                if (MODE == kGatherCount) cnt[c] += in ? 1u : 0u;
                 const double wt = in ? kernel_w(sqrt_nr(r2) * kk.x, kk.y) : 0.0;
                 num[c] = fma(nk, wt, num[c]);
                 den[c] += wt;
@@ -471,7 +461,7 @@ __global__ void __launch_bounds__(kThreads) shepard_gather(start_box box, double
         }
     }
     empty_list();
-    if (MODE == kCountPairs) {
+    if (MODE == kGatherCount) {
 #pragma unroll
         for (int j = 0; j < kCellsZ; ++j) {
             unsigned lo = sl < 4 ? (cnt[j] & 0xFFu) << (8 * sl) : 0u, hi = sl >= 4 ? (cnt[j] & 0xFFu) << (8 * (sl - 4)) : 0u;
@@ -488,7 +478,6 @@ __global__ void __launch_bounds__(kThreads) shepard_gather(start_box box, double
                 pcount[cell0 + j] = total;
             }
         }
-        return;
     }
 #pragma unroll
     for (int j = 0; j < kCellsZ; ++j) {
@@ -786,6 +775,7 @@ void free_bins(Ctx *c, GasBins *b)
     b->bytes = b->bytes2 = b->bytes3 = b->bytes4 = 0;
     b->pcount = b->pstart = b->pidx = nullptr;
     b->pslice = nullptr;
+    b->counted = nullptr;
     b->pw = b->pden = nullptr;
 }
 
@@ -828,14 +818,12 @@ void fill_grid(Ctx *c, const GasBins &b, const double *nhi, Grid *g)
         nullptr, nullptr, nullptr, nullptr, nullptr);
 }
 
-start_status record_pairs(Ctx *c, GasBins *b, Grid *g)
+// 20 bytes a cell for the counts and what the recorded pairs need per cell.
+start_status count_pairs(Ctx *c, GasBins *b, Grid *g)
 {
-    if (b->n == 0 || b->pidx) return START_OK;
     hipStream_t s = c->stream;
     auto al = [](size_t v) { return (v + 255) & ~(size_t)255; };
-    const int64_t ncell = (int64_t)b->G * b->G * b->G;
-    const int64_t ngroups = (ncell + 63) / 64;
-    // 1. pairs per centre, the padded group sizes and their starts
+    const int64_t ncell = (int64_t)b->G * b->G * b->G, ngroups = (ncell + 63) / 64;
     b->bytes3 = al(ncell * sizeof(uint2)) + al(ncell * sizeof(unsigned)) + al((ngroups + 1) * sizeof(unsigned)) +
                 al(scan_temp_bytes(ngroups + 1)) + al(ncell * sizeof(double)) + 256;
     if (dmalloc(c, (void **)&b->mem3, b->bytes3) != hipSuccess) {
@@ -848,40 +836,52 @@ start_status record_pairs(Ctx *c, GasBins *b, Grid *g)
     b->pslice = (uint2 *)take(ncell * sizeof(uint2));
     b->pcount = (unsigned *)take(ncell * sizeof(unsigned));
     b->pstart = (unsigned *)take((ngroups + 1) * sizeof(unsigned));
-    void *scan_tmp = take(scan_temp_bytes(ngroups + 1));
+    b->pscan = take(scan_temp_bytes(ngroups + 1));
     b->pden = (double *)take(ncell * sizeof(double));
-    unsigned long long *d_total = (unsigned long long *)take(256);   // [1]: a slice has too many pairs
+    b->counted = (unsigned long long *)take(256);   // [0] pairs with padding, [1] a slice has more than 255
+    hipMemsetAsync(b->counted, 0, 2 * sizeof(unsigned long long), s);
+    shepard_gather<kGatherCount><<<gather_blocks(b->G), kThreads, 0, s>>>(
+        b->box, b->delta, b->G, b->cls, b->start, b->pos_h, b->kern, b->ns, g->val, g->valf, g->sx, g->sy, b->pslice,
+        b->pcount, nullptr, nullptr, nullptr, nullptr, (unsigned *)(b->counted + 1));
+    return START_OK;
+}
+
+start_status record_pairs(Ctx *c, GasBins *b, const double *nhi, Grid *g)
+{
+    hipStream_t s = c->stream;
+    auto al = [](size_t v) { return (v + 255) & ~(size_t)255; };
+    const int64_t ncell = (int64_t)b->G * b->G * b->G, ngroups = (ncell + 63) / 64;
     auto drop = [&]() {
         dfree(c, b->mem3, b->bytes3);
         b->mem3 = nullptr;
         b->bytes3 = 0;
         b->pcount = b->pstart = nullptr;
         b->pslice = nullptr;
+        b->counted = nullptr;
         b->pden = nullptr;
     };
+    // 1. the padded group sizes, their sum and their starts
     hipMemsetAsync(b->pstart + ngroups, 0, sizeof(unsigned), s);
-    hipMemsetAsync(d_total, 0, 2 * sizeof(unsigned long long), s);
-    shepard_gather<kCountPairs><<<gather_blocks(b->G), kThreads, 0, s>>>(
-        b->box, b->delta, b->G, b->cls, b->start, b->pos_h, b->kern, b->ns, nullptr, nullptr, 0, 0, b->pslice,
-        b->pcount, nullptr, nullptr, nullptr, nullptr, (unsigned *)(d_total + 1));
     group_sizes<<<blocks_for(ngroups), kThreads, 0, s>>>(ncell, ngroups, b->pcount, b->pstart);
-    sum_counts<<<blocks_for(ngroups), kThreads, 0, s>>>(ngroups, b->pstart, d_total);
+    sum_counts<<<blocks_for(ngroups), kThreads, 0, s>>>(ngroups, b->pstart, b->counted);
     unsigned long long words[2] = {0, 0};
-    hipMemcpyAsync(words, d_total, sizeof(words), hipMemcpyDeviceToHost, s);
+    hipMemcpyAsync(words, b->counted, sizeof(words), hipMemcpyDeviceToHost, s);
     if (hipStreamSynchronize(s) != hipSuccess) {
         drop();
         return START_EHIP;
     }
-    const unsigned long long total64 = words[0];
     // the starts are 32-bit, the pairs (12 B each) must stay modest, and a
-    // cell's slices count theirs in bytes
-    if (total64 > kMaxPairs || words[1]) {
+    // cell's slices count theirs in bytes.  (Wider counts gain nothing: a refill
+    // waits for its longest cell, where the search has eight lanes for it.  20
+    // iterations on 2^20 particles, 3000 of them in one cell: 21.1 ms with
+    // recorded pairs, 17.9 without.)
+    if (words[0] > kMaxPairs || words[1]) {
         drop();
         return START_ENOMEM;
     }
-    exclusive_scan_u32(b->pstart, ngroups + 1, scan_tmp, s);
+    exclusive_scan_u32(b->pstart, ngroups + 1, b->pscan, s);
     // 2. the pairs themselves (particle, weight), with the weight sums
-    const size_t np = total64 > 0 ? (size_t)total64 : 1;
+    const size_t np = words[0] > 0 ? (size_t)words[0] : 1;
     b->bytes4 = al(np * sizeof(unsigned)) + al(np * sizeof(double));
     if (dmalloc(c, (void **)&b->mem4, b->bytes4) != hipSuccess) {
         b->mem4 = nullptr;
@@ -890,14 +890,13 @@ start_status record_pairs(Ctx *c, GasBins *b, Grid *g)
         drop();
         return START_ENOMEM;
     }
-    unsigned *pidx = (unsigned *)b->mem4;
+    b->pidx = (unsigned *)b->mem4;
     b->pw = (double *)(b->mem4 + al(np * sizeof(unsigned)));
+    b->n_pairs = (int64_t)words[0];
+    gather_values<<<blocks_for(b->n), kThreads, 0, s>>>(b->n, b->idx, nhi, b->ns);
     shepard_gather<kFillPairs><<<gather_blocks(b->G), kThreads, 0, s>>>(
         b->box, b->delta, b->G, b->cls, b->start, b->pos_h, b->kern, b->ns, g->val, g->valf, g->sx, g->sy, b->pslice,
-        nullptr, b->pstart, pidx, b->pw, b->pden, nullptr);
-    b->pidx = pidx;
-    b->n_pairs = (int64_t)total64;
-    if (hipStreamSynchronize(s) != hipSuccess) return START_EHIP;
+        nullptr, b->pstart, b->pidx, b->pw, b->pden, nullptr);
     return START_OK;
 }
 

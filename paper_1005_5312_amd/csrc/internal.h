@@ -183,6 +183,8 @@ struct GasBins {
     unsigned *pidx = nullptr;    // binned particle of each pair
     double *pw = nullptr;        // kernel weight of each pair
     double *pden = nullptr;      // weight sum of each cell
+    void *pscan = nullptr;       // scan temporary of pstart
+    unsigned long long *counted = nullptr;   // totals (count_pairs)
     int64_t n_pairs = 0;
 };
 
@@ -195,10 +197,14 @@ void free_bins(Ctx *c, GasBins *b);
 // Enqueues the grid values from the binned particles; nhi (particle order,
 // not validated) replaces the binned n_HI first when non-null.
 void fill_grid(Ctx *c, const GasBins &b, const double *nhi, Grid *g);
-// Records the pairs (and fills g from the binned n_HI) so that later
-// fill_grid calls read them instead of searching the stencil; synchronises.
-// START_ENOMEM leaves the bins as they were (fill_grid then gathers).
-start_status record_pairs(Ctx *c, GasBins *b, Grid *g);
+// Fills g from the binned n_HI and counts the pairs on the way, for a
+// record_pairs that may follow.  START_ENOMEM leaves the bins and g as they were.
+start_status count_pairs(Ctx *c, GasBins *b, Grid *g);
+// Records the pairs that count_pairs counted and fills g from nhi (as
+// fill_grid), so that later fill_grid calls read the pairs instead of searching
+// the stencil; waits for the counts.  START_ENOMEM leaves g to fill_grid, which
+// then gathers.
+start_status record_pairs(Ctx *c, GasBins *b, const double *nhi, Grid *g);
 
 // ---- memory helpers (count against the context budget) ----
 hipError_t dmalloc(Ctx *c, void **p, size_t bytes);
