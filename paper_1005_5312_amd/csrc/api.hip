@@ -1461,7 +1461,7 @@ size_t start_estimate_bytes(int64_t n_t, int64_t n_s, int64_t n_gas, int grid_lo
     const int64_t G = (int64_t)1 << grid_log2, pad = (G >= 64 && G <= 512) ? 16 : 0;
     const size_t span = (size_t)((G - 1) * (G * (G + pad) + pad) + (G - 1) * (G + pad) + G);   // padded grid
     // tree: persistent (keys, perm, sources, 2 n_s nodes) + build temporaries
-    const size_t tree = (size_t)n_s * (8 + 4 + 32 + 16) + (size_t)2 * n_s * (16 + 16 + 32 + 16 + 80) +
+    const size_t tree = (size_t)n_s * (8 + 4 + 32 + 16) + (size_t)2 * n_s * (16 + 16 + 32 + 16 + 48) +
                         radix_temp_bytes(n_s) + (size_t)n_s * 22 + (size_t)2 * n_s * 14 + 65536;
     // both grid copies with their guard bands (G <= 512)
     const int64_t sy = G + pad, sx = G * sy + pad;

@@ -78,9 +78,10 @@ struct Ctx {
     size_t ev_used = 0;
 };
 
-// A node among its siblings: the cube as in Tree::bnd, and (node index; place
-// of the first child, or a bucket's first sorted source; flags | kind << 2 |
-// children << 4; a leaf's original source index or a bucket's source count).
+// A node among its siblings: the cube in normalised units (lower corner c
+// 2^-level and side 2^-level), and (node index; place of the first child, or a
+// bucket's first sorted source; flags | kind << 2 | children << 4; a leaf's
+// original source index or a bucket's source count).
 // Flags (set with the FP32 copies): 1 L > 0, 2 L > 0 in FP32.  48 bytes: four
 // lanes read it as three words each.
 struct Sibling {
@@ -95,7 +96,6 @@ struct Tree {
     int64_t n_src = 0;
     int64_t n_nodes = 0;
     int4 *geo = nullptr;       // (cx, cy, cz, level | kind << 8)
-    double4 *bnd = nullptr;    // the cube in normalised units: lower corner (c 2^-level) and side 2^-level
     int *skip = nullptr;       // index of the first node after the subtree
     int *first = nullptr;      // range of the cell in sorted source order
     int *count = nullptr;
@@ -229,6 +229,13 @@ struct SortedPairs {
 };
 size_t radix_temp_bytes(int64_t n);
 SortedPairs radix_sort_pairs(uint64_t *keys, unsigned *vals, int64_t n, int bits, void *temp, hipStream_t s);
+
+// The cube of a node in normalised units: lower corner and side (exact: c < 2^21).
+__device__ inline double4 cube_of(const int4 geo)
+{
+    const double side = __hiloint2double((1023 - (geo.w & 0xFF)) << 20, 0);   // 2^-level
+    return make_double4((double)geo.x * side, (double)geo.y * side, (double)geo.z * side, side);
+}
 
 // ---- rate batches (rates.hip) ----
 // One rate problem as given to the library.

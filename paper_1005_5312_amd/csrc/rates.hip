@@ -44,7 +44,6 @@ struct Item {
     int64_t n_nodes;
     int64_t n_src;
     const int4 *geo;
-    const double4 *bnd;
     const int *skip;
     const int *first;
     const int *count;
@@ -99,8 +98,7 @@ struct Item {
 // closest point of the cube [c 2^-n, (c+1) 2^-n].  Written as the same FP64
 // operations as the oracle (explicit fma, no contraction) so that the lists
 // agree bit for bit.  b = (lo x, lo y, lo z, side): the cube's corner c 2^-n
-// and side 2^-n stored at the tree build (exact, c < 2^21), and lo + side =
-// (c + 1) 2^-n is exact too.
+// and side 2^-n (exact, c < 2^21), and lo + side = (c + 1) 2^-n is exact too.
 __device__ inline bool accept_box(const double4 b, const double u[3], double theta2)
 {
     const double lo[3] = {b.x, b.y, b.z};
@@ -133,11 +131,6 @@ __device__ inline int4 uni_int4(const int4 *a, int i)
 }
 __device__ inline int uni_int(const int *a, int64_t i) { return ((CI *)a)[i]; }
 __device__ inline unsigned uni_u32(const unsigned *a, int64_t i) { return ((CU *)a)[i]; }
-__device__ inline double4 uni_d4(const double4 *a, int i)
-{
-    CD *p = (CD *)a + 4 * (int64_t)i;
-    return make_double4(p[0], p[1], p[2], p[3]);
-}
 __device__ inline void uni_sibling(const Sibling *a, int i, double4 &cube, int4 &meta)
 {
     CD *p = (CD *)a + 6 * (int64_t)i;
@@ -472,7 +465,6 @@ __global__ void __launch_bounds__(kThreads) list_kernel(const Item *__restrict__
         ++n_entries;
     };
     const int4 *const t_geo = P.geo;
-    const double4 *const t_bnd = P.bnd;
     const int *const t_skip = P.skip;
     const int *const t_ref = P.ref;
     const int *const t_first = P.first;
@@ -496,7 +488,7 @@ __global__ void __launch_bounds__(kThreads) list_kernel(const Item *__restrict__
             node += 1;
             continue;
         }
-        const bool acc = active && accept_box(uni_d4(t_bnd, node), u, theta2);
+        const bool acc = active && accept_box(cube_of(g), u, theta2);
         if (acc) {
             emit(node, (uint64_t)node << 32, lw);
             resume = sk;
@@ -1304,7 +1296,6 @@ Item make_item(const RateSpec &r, const BatchScratch &bs, int64_t off)
     I.n_nodes = t->n_nodes;
     I.n_src = t->n_src;
     I.geo = t->geo;
-    I.bnd = t->bnd;
     I.skip = t->skip;
     I.first = t->first;
     I.count = t->count;

@@ -163,8 +163,8 @@ __global__ void tree_readback(const unsigned *count, const unsigned *bflags, uns
 __global__ void __launch_bounds__(kThreads) fill_nodes(int n, const uint64_t *k, const unsigned *perm,
                                                        const int2 *range, const int *delta, const unsigned *levels,
                                                        const unsigned *start, const double4 *src, int4 *geo, int *skip,
-                                                       int *first, int *count, int *ref, double4 *bnd, double4 *mom,
-                                                       double *lscale, unsigned *n_nodes)
+                                                       int *first, int *count, int *ref, double4 *mom, double *lscale,
+                                                       unsigned *n_nodes)
 {
     const int i = blockIdx.x * kThreads + threadIdx.x;
     if (i >= n) return;
@@ -176,9 +176,6 @@ __global__ void __launch_bounds__(kThreads) fill_nodes(int n, const uint64_t *k,
         const uint64_t prefix = level > 0 ? (k[f] >> (3 * (kMaxLevel - level))) : 0ull;
         const int cx = (int)compact3(prefix >> 2), cy = (int)compact3(prefix >> 1), cz = (int)compact3(prefix);
         geo[p] = make_int4(cx, cy, cz, level | (kind << 8));
-        // the cube's lower corner and side in normalised units (exact: c < 2^21)
-        bnd[p] = make_double4(ldexp((double)cx, -level), ldexp((double)cy, -level), ldexp((double)cz, -level),
-                              ldexp(1.0, -level));
         skip[p] = (int)start[f + c];
         first[p] = f;
         count[p] = c;
@@ -425,15 +422,15 @@ __global__ void __launch_bounds__(kThreads) place_children(const unsigned *n_nod
 }
 
 __global__ void __launch_bounds__(kThreads) fill_siblings(const unsigned *n_nodes, const int *order, const int2 *kids,
-                                                          const int4 *geo, const double4 *bnd, const int *first,
-                                                          const int *count, const int *ref, Sibling *sib)
+                                                          const int4 *geo, const int *first, const int *count,
+                                                          const int *ref, Sibling *sib)
 {
     const int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (k >= (int64_t)*n_nodes) return;
     const int p = order[k];
     const int kind = geo[p].w >> 8;
     const int2 kd = kids[p];
-    const double4 b = bnd[p];
+    const double4 b = cube_of(geo[p]);
     sib[k] = Sibling{{b.x, b.y, b.z, b.w},
                      p,
                      kind == kKindBucket ? first[p] : kd.x,
@@ -802,7 +799,7 @@ start_status build_tree(Ctx *c, const start_box &box, int64_t n, const double *x
                            al256(n * sizeof(uint4)) + al256(max_items * sizeof(int4)) +
                            4 * al256(max_items * sizeof(int)) + al256(max_items * sizeof(double4)) +
                            al256(max_items * sizeof(uint4)) + 2 * al256(sizeof(double)) +
-                           al256(max_items * sizeof(double4)) + al256(max_items * sizeof(Sibling));
+                           al256(max_items * sizeof(Sibling));
     char *pm = nullptr;
     if (dmalloc(c, (void **)&pm, persist) != hipSuccess) return START_ENOMEM;
     t->bytes = persist;
@@ -821,7 +818,6 @@ start_status build_tree(Ctx *c, const start_box &box, int64_t n, const double *x
     t->momq = (uint4 *)take(max_items * sizeof(uint4));
     t->lscale = (double *)take(sizeof(double));
     t->d_nodes = (unsigned *)take(sizeof(double));
-    t->bnd = (double4 *)take(max_items * sizeof(double4));
     t->sib = (Sibling *)take(max_items * sizeof(Sibling));
 
     // temporaries
@@ -850,13 +846,12 @@ start_status build_tree(Ctx *c, const start_box &box, int64_t n, const double *x
     radix_tree_kernel<<<blocks_for(n), kThreads, 0, s>>>(t->keys, ni, range, delta, levels);
     exclusive_scan_bits(levels, start, n + 1, scan_tmp, s);   // start[i] = nodes with first < i
     fill_nodes<<<blocks_for(n), kThreads, 0, s>>>(ni, t->keys, t->perm, range, delta, levels, start, t->src, t->geo,
-                                                  t->skip, t->first, t->count, t->ref, t->bnd, t->mom, t->lscale,
-                                                  t->d_nodes);
+                                                  t->skip, t->first, t->count, t->ref, t->mom, t->lscale, t->d_nodes);
     place_children<<<blocks_for(max_items), kThreads, 0, s>>>(t->d_nodes, t->geo, t->skip, t->count, w.lists, w.kids,
                                                               w.order, w.roots, w.cells);
     sum_moments(t, w, s);
-    fill_siblings<<<blocks_for(max_items), kThreads, 0, s>>>(t->d_nodes, w.order, w.kids, t->geo, t->bnd, t->first,
-                                                             t->count, t->ref, t->sib);
+    fill_siblings<<<blocks_for(max_items), kThreads, 0, s>>>(t->d_nodes, w.order, w.kids, t->geo, t->first, t->count,
+                                                             t->ref, t->sib);
     t->n_nodes = max_items;   // (its bound, until it is read back)
     make_fp32_tree(t, s);
     unsigned h[2] = {0, 0};
