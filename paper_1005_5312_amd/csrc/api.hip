@@ -13,7 +13,6 @@ namespace start {
 start_status build_tree(Ctx *c, const start_box &box, int64_t n, const double *xyz, const double *lum, Tree *t);
 start_status build_grid(Ctx *c, const start_box &box, int64_t n, const double *xyz, const double *h,
                         const double *nhi, int grid_log2, Grid *g);
-void make_fp32_tree(Tree *t, hipStream_t s);
 size_t refit_bytes(const Tree *t);
 void refit_prepare(Ctx *c, const Tree *t, void *work);
 void refit_tree(Ctx *c, Tree *t, const double *lum, void *work);

@@ -230,12 +230,20 @@ struct SortedPairs {
 size_t radix_temp_bytes(int64_t n);
 SortedPairs radix_sort_pairs(uint64_t *keys, unsigned *vals, int64_t n, int bits, void *temp, hipStream_t s);
 
+// ---- trees' FP32 copies and sibling records (rates.hip) ----
 // The cube of a node in normalised units: lower corner and side (exact: c < 2^21).
 __device__ inline double4 cube_of(const int4 geo)
 {
     const double side = __hiloint2double((1023 - (geo.w & 0xFF)) << 20, 0);   // 2^-level
     return make_double4((double)geo.x * side, (double)geo.y * side, (double)geo.z * side, side);
 }
+// Redone after the luminosities have changed: the FP32 copies of the virtual
+// sources and the flags of the sibling records.
+void make_fp32_tree(Tree *t, hipStream_t s);
+// The same with the whole sibling records of a new tree of at most max_nodes
+// nodes: order is the node at each place, kids the place and number of a node's
+// children.
+void make_siblings(Tree *t, int64_t max_nodes, const int *order, const int2 *kids, hipStream_t s);
 
 // ---- rate batches (rates.hip) ----
 // One rate problem as given to the library.

@@ -1148,10 +1148,13 @@ __global__ void __launch_bounds__(kThreads) batch_gather(int64_t n, const int64_
 // FP32-path copies of the virtual sources (fixed32 above, with the targets'
 // encoding): the centre as 32-bit fixed-point coordinates of the box and the
 // luminosity relative to the root's (every L' <= 1); and whether the node
-// shines in each precision, in its sibling record.
+// shines in each precision, in its sibling record.  BUILD: the whole record.
+template <bool BUILD>
 __global__ void __launch_bounds__(kThreads) make_fp32(const unsigned *n_nodes, int64_t n, const double4 *mom,
                                                       const double4 *src, const double *lscale, start_box box,
-                                                      double inv, uint4 *momq, Sibling *sib, uint4 *srcq)
+                                                      double inv, uint4 *momq, Sibling *sib, uint4 *srcq,
+                                                      const int *order, const int2 *kids, const int4 *geo,
+                                                      const int *first, const int *count, const int *ref)
 {
     const int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     const double Lref = *lscale;
@@ -1160,11 +1163,24 @@ __global__ void __launch_bounds__(kThreads) make_fp32(const unsigned *n_nodes, i
                           __float_as_uint((float)(v.w / Lref)));
     };
     if (k < (int64_t)*n_nodes) {
-        const int p = sib[k].node;
+        const int p = BUILD ? order[k] : sib[k].node;
         const double4 v = mom[p];
         const uint4 q = encode(v);
         momq[p] = q;
-        sib[k].bits = (sib[k].bits & ~3) | (v.w > 0.0 ? 1 : 0) | (__uint_as_float(q.w) > 0.f ? 2 : 0);
+        const int lit = (v.w > 0.0 ? 1 : 0) | (__uint_as_float(q.w) > 0.f ? 2 : 0);
+        if (BUILD) {
+            const int4 g = geo[p];
+            const int kind = g.w >> 8;
+            const int2 kd = kids[p];
+            const double4 b = cube_of(g);
+            sib[k] = Sibling{{b.x, b.y, b.z, b.w},
+                             p,
+                             kind == kKindBucket ? first[p] : kd.x,
+                             lit | (kind << 2) | (kd.y << 4),
+                             kind == kKindLeaf ? ref[p] : (kind == kKindBucket ? count[p] : 0)};
+        } else {
+            sib[k].bits = (sib[k].bits & ~3) | lit;
+        }
     }
     if (k < n) srcq[k] = encode(src[k]);
 }
@@ -1176,9 +1192,17 @@ inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kThreads - 1) / k
 void make_fp32_tree(Tree *t, hipStream_t s)
 {
     if (t->n_nodes == 0) return;
-    const int64_t k = t->n_nodes > t->n_src ? t->n_nodes : t->n_src;
-    make_fp32<<<blocks_for(k), kThreads, 0, s>>>(t->d_nodes, t->n_src, t->mom, t->src, t->lscale, t->box,
-                                                 1.0 / t->box.size, t->momq, t->sib, t->srcq);
+    const int64_t k = std::max(t->n_nodes, t->n_src);
+    make_fp32<false><<<blocks_for(k), kThreads, 0, s>>>(t->d_nodes, t->n_src, t->mom, t->src, t->lscale, t->box,
+                                                        1.0 / t->box.size, t->momq, t->sib, t->srcq, nullptr, nullptr,
+                                                        nullptr, nullptr, nullptr, nullptr);
+}
+
+void make_siblings(Tree *t, int64_t max_nodes, const int *order, const int2 *kids, hipStream_t s)
+{
+    make_fp32<true><<<blocks_for(max_nodes), kThreads, 0, s>>>(t->d_nodes, t->n_src, t->mom, t->src, t->lscale, t->box,
+                                                               1.0 / t->box.size, t->momq, t->sib, t->srcq, order, kids,
+                                                               t->geo, t->first, t->count, t->ref);
 }
 
 // ------------------------------------------------------------------------

@@ -29,8 +29,6 @@
 
 namespace start {
 
-void make_fp32_tree(Tree *t, hipStream_t s);
-
 namespace {
 
 constexpr int kThreads = 256;
@@ -217,6 +215,11 @@ __global__ void __launch_bounds__(kThreads) sorted_sources(int64_t n, const unsi
 constexpr int kSmallTree = 128;              // sources of a subtree that one wave sums
 constexpr int kSmallNodes = 2 * kSmallTree;  // its nodes at most (2 n - 1)
 
+// Lengths of the lists that place_children makes, in words of one block of 256
+// bytes: children (word 0), subtrees for moments_small, and the cells above them
+// by level, on lines of their own.
+constexpr int kRootWord = 16, kLevelWord = 32, kListWords = kLevelWord + kMaxLevel + 1;
+
 __device__ inline double4 weighted(const double4 s) { return make_double4(s.w * s.x, s.w * s.y, s.w * s.z, s.w); }
 
 __device__ inline double4 plus(const double4 a, const double4 b)
@@ -253,7 +256,7 @@ __global__ void __launch_bounds__(kThreads) moments_small(const int *lists, cons
     const int w = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
     double4 *const sum = sum_all[w];
     int *const end = end_all[w];
-    const int n_roots = lists[1];
+    const int n_roots = lists[kRootWord];
     constexpr int kPer = kSmallNodes / 64;
     for (int64_t t = (int64_t)blockIdx.x * (kThreads / 64) + w; t < n_roots; t += (int64_t)gridDim.x * (kThreads / 64)) {
         const int2 r = roots[t];   // (node, first node after the subtree)
@@ -302,75 +305,97 @@ __global__ void __launch_bounds__(kThreads) moments_small(const int *lists, cons
     }
 }
 
-// The cells of more than kSmallTree sources, by one block, level by level from
-// the deepest (their children are among them, single sources, or subtrees that
+// The cells of more than kSmallTree sources, level by level from the deepest
+// (their children are among them, single sources, or subtrees that
 // moments_small has summed).  The children are read through their places
 // (place_children), all at once: the chain of links between them would be
 // eight dependent loads.
-constexpr int kTopThreads = 1024;
-__global__ void __launch_bounds__(kTopThreads) moments_top(const int *lists, const int *cells, const int2 *kids,
-                                                           const int *order, const int4 *geo, const int *first,
-                                                           const int *count, const double4 *src, double4 *msum,
-                                                           double4 *mom, double *lscale)
+struct TopCells {
+    const int *lists, *cells;   // cap places a level
+    int cap;
+    const int2 *kids;
+    const int *order;
+    const int4 *geo;
+    const int *first, *count;
+    const double4 *src;
+    double4 *msum, *mom;
+    double *lscale;
+};
+
+__device__ inline void sum_cell(const TopCells &c, int p)
 {
-    __shared__ int deepest;
-    const int n = lists[2];
-    if (threadIdx.x == 0) deepest = -1;
-    __syncthreads();
-    for (int t = (int)threadIdx.x; t < n; t += kTopThreads) atomicMax(&deepest, geo[cells[t]].w & 0xFF);
-    __syncthreads();
-    for (int lv = deepest; lv >= 0; --lv) {
-        for (int t = (int)threadIdx.x; t < n; t += kTopThreads) {
-            const int p = cells[t];
-            const int gw = geo[p].w;
-            if ((gw & 0xFF) != lv) continue;
-            double4 s = make_double4(0.0, 0.0, 0.0, 0.0);
-            if ((gw >> 8) == kKindBucket) {
-                s = bucket_sum(src, first[p], count[p]);
-            } else {
-                const int2 kd = kids[p];
-                int kid[8];
-                bool leaf[8];
-                double4 v[8];
+    double4 s = make_double4(0.0, 0.0, 0.0, 0.0);
+    if ((c.geo[p].w >> 8) == kKindBucket) {
+        s = bucket_sum(c.src, c.first[p], c.count[p]);
+    } else {
+        const int2 kd = c.kids[p];
+        int kid[8];
+        bool leaf[8];
+        double4 v[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) kid[j] = order[kd.x + (j < kd.y ? j : 0)];
+        for (int j = 0; j < 8; ++j) kid[j] = c.order[kd.x + (j < kd.y ? j : 0)];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) leaf[j] = (geo[kid[j]].w >> 8) == kKindLeaf;
+        for (int j = 0; j < 8; ++j) leaf[j] = (c.geo[kid[j]].w >> 8) == kKindLeaf;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) v[j] = leaf[j] ? src[first[kid[j]]] : msum[kid[j]];
+        for (int j = 0; j < 8; ++j) v[j] = leaf[j] ? c.src[c.first[kid[j]]] : c.msum[kid[j]];
 #pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    if (j < kd.y) s = plus(s, leaf[j] ? weighted(v[j]) : v[j]);
-            }
-            msum[p] = s;
-            mom[p] = centre_of(s);
-            if (p == 0) lscale[0] = unit_of(s.w);
-        }
+        for (int j = 0; j < 8; ++j)
+            if (j < kd.y) s = plus(s, leaf[j] ? weighted(v[j]) : v[j]);
+    }
+    c.msum[p] = s;
+    c.mom[p] = centre_of(s);
+    if (p == 0) c.lscale[0] = unit_of(s.w);
+}
+
+// All levels by one block up to kOneBlock sources, where a launch per level
+// would take longer (a build of 2^18 sources 320 us, 351 by levels); by levels
+// beyond, where one CU is too few (2^19 sources 483 us by one block and 451 by
+// levels, 2^20 741 and 603, 2^22 2949 and 1946).
+constexpr int kTopThreads = 1024;
+constexpr int64_t kOneBlock = (int64_t)3 << 17;
+__global__ void __launch_bounds__(kTopThreads) moments_top(TopCells c)
+{
+    for (int lv = kMaxLevel; lv >= 0; --lv) {
+        const int n = c.lists[kLevelWord + lv];
+        if (n == 0) continue;
+        for (int t = (int)threadIdx.x; t < n; t += kTopThreads) sum_cell(c, c.cells[(int64_t)lv * c.cap + t]);
         __threadfence_block();
         __syncthreads();
     }
 }
 
+__global__ void __launch_bounds__(kThreads) moments_level(TopCells c, int lv)
+{
+    const int n = c.lists[kLevelWord + lv];
+    for (int t = (int)(blockIdx.x * kThreads + threadIdx.x); t < n; t += (int)gridDim.x * kThreads)
+        sum_cell(c, c.cells[(int64_t)lv * c.cap + t]);
+}
+
 // ---- siblings side by side ----------------------------------------------
 // Places of every cell's children (at most eight, in depth-first order), and
-// the two lists of the moment sums: the largest subtrees of at most
-// kSmallTree sources (node, end) and the cells above them.  A block takes one
-// run of each for its 256 nodes (lists: [0] children, [1] subtrees, [2] cells
-// placed so far), so which run a cell gets depends on the schedule, its
-// contents do not.
-__global__ void __launch_bounds__(kThreads) place_children(const unsigned *n_nodes, const int4 *geo, const int *skip,
-                                                           const int *count, int *lists, int2 *kids, int *order,
-                                                           int2 *roots, int *cells)
+// the lists of the moment sums: the largest subtrees of at most kSmallTree
+// sources (node, end) and the cells above them (cells: cap places a level).  A
+// block takes one run of each for its nodes, so which run a cell gets depends
+// on the schedule, its contents do not.  Blocks of 1024: every block adds to
+// the same few words (2^22 sources, blocks of 256: 289 us, now 125).
+constexpr int kPlaceThreads = 1024;
+__global__ void __launch_bounds__(kPlaceThreads) place_children(const unsigned *n_nodes, const int4 *geo,
+                                                                const int *skip, const int *count, int *lists,
+                                                                int2 *kids, int *order, int2 *roots, int *cells,
+                                                                int cap)
 {
-    __shared__ uint64_t wtot[kThreads / 64];
-    __shared__ int run[3];
+    constexpr int kWaves = kPlaceThreads / 64;
+    __shared__ unsigned wtot[kWaves];
+    __shared__ int run[2], level_n[kMaxLevel + 1], level_run[kMaxLevel + 1];
     const int64_t m = *n_nodes;
-    const int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const int64_t p = (int64_t)blockIdx.x * kPlaceThreads + threadIdx.x;
     const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
+    if (threadIdx.x <= kMaxLevel) level_n[threadIdx.x] = 0;
     int kid[8], kend[8];
     int k = 0;
     unsigned small = 0;                 // children that root a small subtree
-    const int kind = p < m ? geo[p].w >> 8 : kKindLeaf;
+    const int gw = p < m ? geo[p].w : kKindLeaf << 8;
+    const int kind = gw >> 8, level = gw & 0xFF;
     const bool big = kind != kKindLeaf && count[p] > kSmallTree;
     if (kind == kKindInternal) {
         const int end = skip[p];
@@ -388,30 +413,36 @@ __global__ void __launch_bounds__(kThreads) place_children(const unsigned *n_nod
         }
     }
     const bool small_root = p == 0 && kind != kKindLeaf && !big;
-    // one scan of the three numbers, 16 bits each (at most 8 * 256)
-    const uint64_t mine = (uint64_t)k | (uint64_t)(__popc(small) + (small_root ? 1 : 0)) << 16 |
-                          (uint64_t)(big ? 1 : 0) << 32;
-    uint64_t incl = mine;
+    // one scan of the two numbers, 16 bits each (at most 8 * 1024)
+    const unsigned mine = (unsigned)k | (unsigned)(__popc(small) + (small_root ? 1 : 0)) << 16;
+    unsigned incl = mine;
     for (int o = 1; o < 64; o <<= 1) {
-        const uint64_t v = __shfl_up((unsigned long long)incl, o, 64);
+        const unsigned v = __shfl_up(incl, o, 64);
         if (lane >= o) incl += v;
     }
     if (lane == 63) wtot[w] = incl;
     __syncthreads();
-    if (threadIdx.x < 3) {
-        uint64_t total = 0;
-        for (int v = 0; v < kThreads / 64; ++v) total += wtot[v];
+    int at_level = 0;
+    if (big) at_level = atomicAdd(&level_n[level], 1);
+    if (threadIdx.x < 2) {
+        unsigned total = 0;
+        for (int v = 0; v < kWaves; ++v) total += wtot[v];
         const int mine_total = (int)((total >> (16 * threadIdx.x)) & 0xFFFFu);
-        run[threadIdx.x] = mine_total ? atomicAdd(&lists[threadIdx.x], mine_total) : 0;
+        run[threadIdx.x] = mine_total ? atomicAdd(&lists[threadIdx.x ? kRootWord : 0], mine_total) : 0;
     }
     __syncthreads();
-    uint64_t before = incl - mine;
+    if (threadIdx.x <= kMaxLevel) {
+        const int n = level_n[threadIdx.x];
+        level_run[threadIdx.x] = n ? atomicAdd(&lists[kLevelWord + threadIdx.x], n) : 0;
+    }
+    __syncthreads();
+    unsigned before = incl - mine;
     for (int v = 0; v < w; ++v) before += wtot[v];
     const int at = 1 + run[0] + (int)(before & 0xFFFFu);   // place 0 is the root's
-    int rt = run[1] + (int)((before >> 16) & 0xFFFFu);
+    int rt = run[1] + (int)(before >> 16);
     if (p < m) kids[p] = make_int2(at, k);
     if (p == 0) order[0] = 0;
-    if (big) cells[run[2] + (int)((before >> 32) & 0xFFFFu)] = (int)p;
+    if (big) cells[(int64_t)level * cap + level_run[level] + at_level] = (int)p;
     if (small_root) roots[rt++] = make_int2(0, skip[0]);
 #pragma unroll
     for (int j = 0; j < 8; ++j)
@@ -419,23 +450,6 @@ __global__ void __launch_bounds__(kThreads) place_children(const unsigned *n_nod
             order[at + j] = kid[j];
             if ((small >> j) & 1u) roots[rt++] = make_int2(kid[j], kend[j]);
         }
-}
-
-__global__ void __launch_bounds__(kThreads) fill_siblings(const unsigned *n_nodes, const int *order, const int2 *kids,
-                                                          const int4 *geo, const int *first, const int *count,
-                                                          const int *ref, Sibling *sib)
-{
-    const int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (k >= (int64_t)*n_nodes) return;
-    const int p = order[k];
-    const int kind = geo[p].w >> 8;
-    const int2 kd = kids[p];
-    const double4 b = cube_of(geo[p]);
-    sib[k] = Sibling{{b.x, b.y, b.z, b.w},
-                     p,
-                     kind == kKindBucket ? first[p] : kd.x,
-                     (kind << 2) | (kd.y << 4),
-                     kind == kKindLeaf ? ref[p] : (kind == kKindBucket ? count[p] : 0)};
 }
 
 // ---- kernel-weighted node luminosities (section 2.2.2) -----------------
@@ -613,7 +627,7 @@ namespace {
 
 // Work arrays of the moment sums of a tree of n sources (at most m nodes):
 // sums, the lists' lengths, and the lists (a small subtree has 2 sources or
-// more; at each of at most 22 levels there are fewer than n / kSmallTree cells
+// more; at each of at most 22 levels there are at most n / kSmallTree cells
 // above them).
 struct Moments {
     double4 *msum;
@@ -624,13 +638,13 @@ struct Moments {
     int *order;
 };
 
-int64_t top_cells_bound(int64_t n) { return 22 * (n / kSmallTree) + 1; }
+int64_t top_cells_bound(int64_t n) { return n / kSmallTree + 1; }   // of one level
 
 size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 size_t list_bytes(int64_t n, int64_t m)
 {
-    return 256 + al256((size_t)(n / 2 + 1) * sizeof(int2)) + al256((size_t)top_cells_bound(n) * sizeof(int)) +
+    return 256 + al256((size_t)(n / 2 + 1) * sizeof(int2)) + al256((size_t)(kMaxLevel + 1) * top_cells_bound(n) * sizeof(int)) +
            al256((size_t)m * sizeof(int2)) + al256((size_t)m * sizeof(int));
 }
 
@@ -650,7 +664,7 @@ Moments carve_moments(void *lists, double4 *msum, int64_t n, int64_t m)
     w.msum = msum;
     w.lists = (int *)take(256);
     w.roots = (int2 *)take((size_t)(n / 2 + 1) * sizeof(int2));
-    w.cells = (int *)take((size_t)top_cells_bound(n) * sizeof(int));
+    w.cells = (int *)take((size_t)(kMaxLevel + 1) * top_cells_bound(n) * sizeof(int));
     w.kids = (int2 *)take((size_t)m * sizeof(int2));
     w.order = (int *)take((size_t)m * sizeof(int));
     return w;
@@ -666,9 +680,24 @@ void sum_moments(Tree *t, const Moments &w, hipStream_t s)
     const unsigned nb = (unsigned)std::min<int64_t>((waves + kThreads / 64 - 1) / (kThreads / 64), 65536);
     moments_small<<<nb, kThreads, 0, s>>>(w.lists, w.roots, t->geo, t->skip, t->first, t->count, t->src, w.msum,
                                           t->mom, t->lscale);
-    if (n > kSmallTree)
-        moments_top<<<1, kTopThreads, 0, s>>>(w.lists, w.cells, w.kids, w.order, t->geo, t->first, t->count, t->src,
-                                              w.msum, t->mom, t->lscale);
+    if (n <= kSmallTree) return;
+    const TopCells c{w.lists, w.cells, (int)top_cells_bound(n), w.kids, w.order, t->geo,
+                     t->first, t->count, t->src, w.msum, t->mom, t->lscale};
+    if (n <= kOneBlock) {
+        moments_top<<<1, kTopThreads, 0, s>>>(c);
+        return;
+    }
+    const unsigned lb = std::min(blocks_for(c.cap), 1024u);
+    for (int lv = kMaxLevel; lv >= 0; --lv) moments_level<<<lb, kThreads, 0, s>>>(c, lv);
+}
+
+// m: the number of nodes, or a bound
+void list_children(const Tree *t, const Moments &w, int64_t m, hipStream_t s)
+{
+    hipMemsetAsync(w.lists, 0, kListWords * sizeof(int), s);
+    place_children<<<(unsigned)((m + kPlaceThreads - 1) / kPlaceThreads), kPlaceThreads, 0, s>>>(
+        t->d_nodes, t->geo, t->skip, t->count, w.lists, w.kids, w.order, w.roots, w.cells,
+        (int)top_cells_bound(t->n_src));
 }
 
 }  // namespace
@@ -684,9 +713,7 @@ void refit_prepare(Ctx *c, const Tree *t, void *work)
     const int64_t m = t->n_nodes;
     if (m == 0) return;
     const Moments w = carve_moments((char *)work + al256((size_t)m * sizeof(double4)), (double4 *)work, t->n_src, m);
-    hipMemsetAsync(w.lists, 0, 3 * sizeof(int), c->stream);
-    place_children<<<blocks_for(m), kThreads, 0, c->stream>>>(t->d_nodes, t->geo, t->skip, t->count, w.lists, w.kids,
-                                                              w.order, w.roots, w.cells);
+    list_children(t, w, m, c->stream);
 }
 
 // The same tree for new luminosities of the same sources: keys, order and
@@ -839,7 +866,6 @@ start_status build_tree(Ctx *c, const start_box &box, int64_t n, const double *x
 
     unsigned *bflags = c->d_flags + 1;   // build validation word (not the rate calls' one)
     hipMemsetAsync(bflags, 0, sizeof(unsigned), s);
-    hipMemsetAsync(w.lists, 0, 3 * sizeof(int), s);
     launch_keys(box, n, xyz, lum, t->keys, t->perm, bflags, s);
     radix_sort_pairs(t->keys, t->perm, n, 63, radix_tmp, s);   // eight passes: the result ends in place
     sorted_sources<<<blocks_for(n + 1), kThreads, 0, s>>>(n, t->perm, xyz, lum, t->src, levels);
@@ -847,13 +873,9 @@ start_status build_tree(Ctx *c, const start_box &box, int64_t n, const double *x
     exclusive_scan_bits(levels, start, n + 1, scan_tmp, s);   // start[i] = nodes with first < i
     fill_nodes<<<blocks_for(n), kThreads, 0, s>>>(ni, t->keys, t->perm, range, delta, levels, start, t->src, t->geo,
                                                   t->skip, t->first, t->count, t->ref, t->mom, t->lscale, t->d_nodes);
-    place_children<<<blocks_for(max_items), kThreads, 0, s>>>(t->d_nodes, t->geo, t->skip, t->count, w.lists, w.kids,
-                                                              w.order, w.roots, w.cells);
+    list_children(t, w, max_items, s);
     sum_moments(t, w, s);
-    fill_siblings<<<blocks_for(max_items), kThreads, 0, s>>>(t->d_nodes, w.order, w.kids, t->geo, t->first, t->count,
-                                                             t->ref, t->sib);
-    t->n_nodes = max_items;   // (its bound, until it is read back)
-    make_fp32_tree(t, s);
+    make_siblings(t, max_items, w.order, w.kids, s);
     unsigned h[2] = {0, 0};
     if (c->rb) {
         tree_readback<<<1, 64, 0, s>>>(t->d_nodes, bflags, c->rb_dev);
