@@ -14,6 +14,8 @@
 // taken by pointer jumping: after round k every pair holds the sum of its
 // first 3^k links (two links a round).  A few rounds shorten every chain, and
 // the rates walk what is left of them.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace start {
@@ -347,6 +349,7 @@ using CD = const __attribute__((address_space(4))) double;
 using CU = const __attribute__((address_space(4))) unsigned;
 
 constexpr int64_t kWavePairs = 48;   // pairs per particle from which a wave takes a particle
+constexpr int64_t kWaves = 16384;    // waves that fill the chip twice
 
 template <bool BITS, bool WAVE>
 __device__ __forceinline__ void find_upstream(
@@ -535,21 +538,24 @@ __global__ void __launch_bounds__(kThreads) upstream_parent(
                                sigma, ucm, links, roots, n_roots);
 }
 
+// parts: waves that share a particle's pairs, 64 in turn
 __global__ void __launch_bounds__(kThreads) upstream_parent_wave(
-    int64_t n, const unsigned *__restrict__ perm, const double *__restrict__ xyz, const double *__restrict__ nhi,
+    int64_t n, unsigned parts, const unsigned *__restrict__ perm, const double *__restrict__ xyz, const double *__restrict__ nhi,
     const uint2 *__restrict__ sl, const uint64_t *__restrict__ keys, const unsigned *__restrict__ nb_off,
     const NbRec *__restrict__ rec, const double4 *__restrict__ mom, const double4 *__restrict__ src,
     const int *__restrict__ first, int64_t n_nodes, const unsigned *__restrict__ bits, double sigma, double ucm,
     Link *__restrict__ links, unsigned *__restrict__ roots, unsigned *__restrict__ n_roots)
 {
-    const int64_t w = xcd_block() * (kThreads / 64) + (threadIdx.x >> 6);
+    // (below 2^31: several parts are taken up to kWaves in all)
+    const unsigned w = (unsigned)__builtin_amdgcn_readfirstlane((int)(xcd_block() * (kThreads / 64) + (threadIdx.x >> 6)));
     const unsigned lane = threadIdx.x & 63u;
-    if (w >= n) return;         // whole waves leave together
-    const unsigned i = (unsigned)__builtin_amdgcn_readfirstlane((int)perm[w]);
+    if (w >= (unsigned)n * parts) return;   // whole waves leave together
+    const unsigned part = parts > 1 ? w % parts : 0u;
+    const unsigned i = (unsigned)__builtin_amdgcn_readfirstlane((int)perm[parts > 1 ? w / parts : w]);
     const uint2 r = sl[i];
     const unsigned p0 = (unsigned)__builtin_amdgcn_readfirstlane((int)r.x);
     const unsigned np = (unsigned)__builtin_amdgcn_readfirstlane((int)r.y);
-    for (unsigned c = 0; c < np; c += 64) {
+    for (unsigned c = part * 64; c < np; c += parts * 64) {
         const bool active = c + lane < np;
         find_upstream<true, true>(i, (int64_t)p0 + (active ? c + lane : np - 1), active, n, xyz, nhi, sl, keys, nb_off,
                                   rec, mom, src, first, n_nodes, bits, sigma, ucm, links, roots, n_roots);
@@ -737,10 +743,16 @@ void launch_upstream_parent(Ctx *c, const Tree *t, int64_t n_pairs, int64_t n, c
 {
     if (n_pairs <= 0) return;
     const double ucm = t->box.length_unit_cm;
-    if (bits && n_pairs >= kWavePairs * n)
-        upstream_parent_wave<<<blocks_for(n * 64), kThreads, 0, c->stream>>>(
-            n, perm, xyz, nhi, sl, keys, nb_off, (const NbRec *)rec, t->mom, t->src, t->first, t->n_nodes, bits, sigma,
-            ucm, (Link *)links, roots, n_roots);
+    if (bits && n_pairs >= kWavePairs * n) {
+        // few particles with long lists: several waves take one, as many as
+        // fill the chip twice (100 particles of 10^5 pairs each: the search
+        // takes 11.5 ms with one wave a particle, 0.34 so)
+        const int64_t per = (n_pairs + 64 * n - 1) / (64 * n);
+        const unsigned parts = (unsigned)std::max<int64_t>(1, std::min<int64_t>(per, kWaves / n));
+        upstream_parent_wave<<<blocks_for(n * parts * 64), kThreads, 0, c->stream>>>(
+            n, parts, perm, xyz, nhi, sl, keys, nb_off, (const NbRec *)rec, t->mom, t->src, t->first, t->n_nodes, bits,
+            sigma, ucm, (Link *)links, roots, n_roots);
+    }
     else if (bits)
         upstream_parent<true><<<blocks_for(n_pairs), kThreads, 0, c->stream>>>(
             n_pairs, n, xyz, nhi, sl, keys, owner, nb_off, (const NbRec *)rec, t->mom, t->src, t->first, t->n_nodes,
