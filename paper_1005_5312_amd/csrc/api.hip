@@ -166,20 +166,6 @@ start_status ensure_stage(start_ctx *ctx, size_t bytes)
     return START_OK;
 }
 
-int size_class(int64_t v, int top)
-{
-    int k = 0;
-    while (k < top && ((int64_t)1 << k) < v) ++k;
-    return k;
-}
-
-// Total targets and largest source count of a batch (the autotuning key),
-// the targets of its largest item, and whether any item is FP64.
-struct BatchSize {
-    int64_t total = 0, max_src = 0, max_t = 0;
-    bool fp64 = false;
-};
-
 BatchSize batch_size(const RateSpec *specs, int n)
 {
     BatchSize b;
@@ -187,51 +173,19 @@ BatchSize batch_size(const RateSpec *specs, int n)
         b.total += specs[i].n_t;
         b.max_t = std::max(b.max_t, specs[i].n_t);
         b.max_src = std::max(b.max_src, specs[i].tree->n_src);
+        b.theta = std::max(b.theta, specs[i].theta);
         b.fp64 |= specs[i].prec == START_FP64;
     }
     return b;
 }
 
-// Targets per wave by size.  Small calls take about total / 4096 (a power of
-// two, at most 8), which keeps ~4096 waves in flight.  Beyond, a larger tile
-// marches more rays of each source side by side, and a smaller one balances the
-// chip's 8192 waves better, the more so the longer its walk is.  Measured (us,
-// tiles of 8 / 16 / 32 / 64, theta = 1, FP32C): every particle a source, 2^17
-// targets 1606 / 1685 / 1892 / 2402, 2^18 2972 / 2955 / 3364 / 3554, 370000
-// 8550 / 7846 / 8099 / 8785, 2^19 11240 / 10580 / 10370 / 10970, 2^20 21580 /
-// 19620 / 18520 / 18870; 1024 sources, 2^16 527 / 537 / 631 / 912, 2^17 954 /
-// 930 / 945 / 1109, 2^18 1713 / 1579 / 1642 / 1700; 64 sources, 2^15 70 / 74 /
-// 106 / 178, 2^16 221 / 192 / 196 / 272, 2^17 376 / 336 / 335 / 346, 2^18 666 /
-// 582 / 574 / 575.  The limits are on the largest item, since a batch's scenes
-// are walked apart, and on the total, which fills the chip: scenes of 16384
-// targets with 1, 64 or 16384 sources take 1087 / 1124 / 1428 / 1570 us at 2^18
-// targets in all, 2987 / 2848 / 3121 / 3423 at 2^20, 10640 / 9760 / 9869 / 9440
-// at 2^22 (scenes of 4096: 805 / 863 / 918 / 1196, 2509 / 2419 / 2603 / 2773,
-// 9387 / 8700 / 8593 / 8309).  The same lines hold in FP64, but for 64: 2^20 targets of
-// 1024 sources take 11150 / 10650 with 32 / 64 (FP32C 10600 / 10680), and
-// FP32C gains from it only beyond 1.5 million (2^21: 34720 / 33410).  With few
-// sources a tile has enough targets to fill a batch of 64 rays (one source,
-// 2^16 targets: 15 us with 64, 33 with 8).
-int tile_from_size(const BatchSize &b)
-{
-    const int small_log2 = b.max_src < 1024 ? 15 : b.max_src < 4096 ? 16 : 17;
-    int h = 1;
-    if (b.max_t <= ((int64_t)1 << small_log2) && b.total <= ((int64_t)1 << 19))
-        while (h < 8 && (int64_t)h * 2 * 4096 <= b.total) h *= 2;
-    else if (b.max_t <= ((int64_t)1 << 18) && b.total < ((int64_t)1 << 22))
-        h = b.total < ((int64_t)1 << 21) ? 16 : 32;
-    else h = b.total < (b.fp64 ? (int64_t)1 << 20 : (int64_t)3 << 19) ? 32 : 64;
-    while (h < 64 && h * b.max_src < 64) h *= 2;
-    return h;
-}
-
-// Targets per wavefront: the fixed choice, else the autotuned one for the
-// size class, else from the size.
+// Targets per wavefront: the fixed choice, else the autotuned one of such
+// batches, else from the size.
 int tile_for(const Ctx &c, const BatchSize &b)
 {
     if (c.tile_fixed > 0) return c.tile_fixed;
-    const int t = c.tile_by_class[size_class(b.total, 39)][size_class(b.max_src, 31)];
-    return t > 0 ? t : tile_from_size(b);
+    const auto tuned = c.tile_tuned.find(tile_class(b));
+    return tuned != c.tile_tuned.end() ? tuned->second : tile_from_size(b);
 }
 
 // The tile size of a batch, with the scratch and staging it needs in place.
@@ -1446,7 +1400,7 @@ start_status start_autotune_rates(start_ctx *ctx, int n_items, const start_item 
     if (st) return st;
     st = start_synchronize(ctx);
     if (st) return st;
-    c.tile_by_class[size_class(size.total, 39)][size_class(size.max_src, 31)] = best;
+    c.tile_tuned[tile_class(size)] = best;
     if (best_tile) *best_tile = best;
     if (best_ms) *best_ms = best_t;
     return START_OK;

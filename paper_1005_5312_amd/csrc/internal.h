@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <map>
 #include <mutex>
 #include <string>
 #include <utility>
@@ -11,6 +12,7 @@
 
 #include "../../include/start.h"
 #include "limits.h"
+#include "tiles.h"
 
 namespace start {
 
@@ -46,11 +48,10 @@ struct Ctx {
     void *host_stage = nullptr;
     size_t host_stage_bytes = 0;
     hipEvent_t stage_ev = nullptr;
-    // targets per wave of the rate kernels: fixed (1..64), or 0 = from the
-    // autotuned table by size class (ceil(log2) of the total targets and of
-    // the largest tree's sources; 0 entries: chosen from the size)
+    // targets per wave of the rate kernels: fixed (1..64), or 0 = the autotuned
+    // choice of the batch's size class, else chosen from the size
     int tile_fixed = 0;
-    int tile_by_class[40][32] = {};
+    std::map<TileClass, int> tile_tuned;
     // replay repeated kernel sequences (the equilibrium iterations) from a
     // captured HIP graph
     bool graphs = true;
