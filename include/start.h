@@ -196,7 +196,11 @@ start_status start_compute_dissociation_rates(start_ctx *ctx, const start_tree *
  * own list and is nearest to the ray (largest cos phi, lowest j on ties);
  *   tau_i = tau_j + sigma (d_i - d_j) (n_HI,i + n_HI,j) / 2,
  * and pairs without one (list-boundary particles) integrate along the ray
- * through `grid`.  FP64.  gas_xyz [3][n_gas], gas_h [n_gas] > 0 (SPH
+ * through `grid`.  (A neighbour exactly at the position of alpha has no angle,
+ * cos phi = 0 / 0: whether it is taken depends on the order in which the
+ * neighbours are visited, which follows the grid's cells.  Sources at particle
+ * positions without self_src have such pairs: every particle's own source is
+ * then in its neighbours' lists.)  FP64.  gas_xyz [3][n_gas], gas_h [n_gas] > 0 (SPH
  * smoothing lengths: 2h is the neighbour radius), gas_nhi [n_gas] >= 0 (the
  * particles' own n_HI), self_src as start_compute_rates.  gamma_out [n_gas]
  * double.  offsets_out [n_gas+1] (host or device, may be NULL) receives the

@@ -329,7 +329,9 @@ __global__ void __launch_bounds__(kThreads) member_bits(int64_t n_pairs, const u
 // wider than their rounding (d2_j below d2_i by more than 1e-14 relative;
 // dot^2 d2_best against dot_best^2 d2_j by more than 1e-13, both dots
 // positive) and falls back to the rounded values themselves otherwise, so
-// the choice is the definition's bit for bit.
+// the choice is the definition's bit for bit.  (But for a neighbour exactly at
+// the source, d_j = 0, whose cos phi is 0 / 0: it is taken if it comes first
+// among those that would be, and then stays.)
 //
 // Membership of the source in a neighbour's list: BITS = false searches the
 // neighbour's sorted list for every neighbour that would be taken (the
