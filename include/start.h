@@ -313,7 +313,9 @@ start_status start_equilibrium_update(start_ctx *ctx, int64_t n, const double *n
 /* Photoionisation equilibrium of the gas around the fixed sources of `tree`,
  * by fixed-point iteration: grid n_HI = x n_H (as start_build_gas_grid, on
  * the tree's box), Gamma of every gas particle (as start_compute_rates with
- * the particles as targets, no self term), then x from
+ * the particles as targets, no self term; in START_FP32C the terms of each sum
+ * are added in another order, depth first, so that a rate may differ from that
+ * call's in its last bits), then x from
  * start_equilibrium_update; stop after the first iteration whose largest
  * change of x is <= tol, or after max_iter.  From a neutral start the
  * iterates decrease monotonically towards the equilibrium; for one source in
@@ -329,8 +331,9 @@ start_status start_equilibrium_update(start_ctx *ctx, int64_t n, const double *n
  * Synchronous (one stream synchronisation per iteration); allocates its
  * grid, particle bins and one n_HI buffer for the duration of the call.  The
  * first iteration stages the rate call (tables, target order); the others
- * repeat its kernels with the grid refill and the update, replayed from one
- * captured HIP graph unless start_set_graph_replay turned graphs off.  The
+ * repeat its kernels with the grid refill and the update, from the third on
+ * replayed from one captured HIP graph unless start_set_graph_replay turned
+ * graphs off.  The
  * context stream must not be used by other threads during the call. */
 start_status start_ionization_equilibrium(start_ctx *ctx, const start_tree *tree, int64_t n_gas,
                                           const double *gas_xyz, const double *gas_h, const double *n_h,
@@ -345,7 +348,8 @@ start_status start_ionization_equilibrium(start_ctx *ctx, const start_tree *tree
  * put the new luminosities into it and redo its moments, which gives the
  * rebuilt tree bit for bit), grids n_HI = x n_H,
  * evaluates Gamma of every particle from every other emitter (self
- * excluded, k_other of eqs. 25-26) and solves
+ * excluded, k_other of eqs. 25-26; START_FP32C rates summed as in
+ * start_ionization_equilibrium) and solves
  *   x Gamma = alpha_eff n_H (1 - x)^2,  alpha_eff = alpha_A - alpha_1 (1 - exp(-tau_self)),
  * i.e. k_other + k_self = alpha_A n_e n_p with k_self of eq. (30) taking its
  * optical depth (eq. 28) from the previous iterate.  Stops as
