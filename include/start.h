@@ -263,8 +263,8 @@ start_status start_rates_plan_free(start_ctx *ctx, start_plan *plan);
  * a tile of up to tile_targets targets and marches the rays of
  * that tile 64 at a time.  1 <= tile_targets <= 64 fixes the tile size for
  * every call on the context; 0 (the default) takes it from the autotuned
- * table, or else chooses it from the numbers of targets and sources, the
- * precision and the opening angle (about total / 4096, at most 8, for small
+ * table, or else chooses it from the numbers of targets and sources, the grid,
+ * the precision and the opening angle (about total / 4096, at most 8, for small
  * calls, so that they still fill the GPU; 16 to 64 beyond).  List exports
  * take about total / 4096, at most 64.  Results do not depend on the tile
  * size (bit for bit). */
@@ -275,9 +275,9 @@ start_status start_set_tile_targets(start_ctx *ctx, int tile_targets);
  * each, the size it would take by itself first (a size twice as slow as the
  * best so far on its first run is not repeated), and records the fastest for
  * the batch's size class in the context's table: total targets, largest
- * item's targets and largest source count, each rounded up to a power of two,
- * any FP64 item or none, and whether every opening angle is below 0.4 with
- * 256 to 4095 sources.  The size it would take by itself is kept unless
+ * item's targets, largest source count and largest grid (16^3 and smaller,
+ * 32^3, larger), each rounded up to a power of two, any FP64 item or none, and
+ * whether every opening angle is below 0.4 with 256 to 4095 sources.  The size it would take by itself is kept unless
  * another is at least 3% faster.  best_tile
  * and best_ms (host, may be NULL) receive the choice and its mean time.
  * Synchronous. */

@@ -174,6 +174,7 @@ BatchSize batch_size(const RateSpec *specs, int n)
         b.max_t = std::max(b.max_t, specs[i].n_t);
         b.max_src = std::max(b.max_src, specs[i].tree->n_src);
         b.theta = std::max(b.theta, specs[i].theta);
+        b.grid = std::max(b.grid, specs[i].grid ? specs[i].grid->G : 1);
         b.fp64 |= specs[i].prec == START_FP64;
     }
     return b;

@@ -8,10 +8,11 @@
 
 namespace start {
 
-// What the choice is made from: a batch's targets, its largest item's targets
-// and sources, its largest opening angle, and whether any item is FP64.
+// What the choice is made from: a batch's targets, its largest item's targets,
+// sources and grid side, its largest opening angle, and whether any item is FP64.
 struct BatchSize {
     int64_t total = 0, max_src = 0, max_t = 0;
+    int grid = 0;
     double theta = 0.0;
     bool fp64 = false;
 };
@@ -52,14 +53,26 @@ inline bool long_lists(const BatchSize &b) { return b.theta < 0.4 && b.max_src >
 //   28629 / 27819, 2^20 - / 57570 / 53620; 64 sources, 2^19: 3650 / 3840 with 32 /
 //   64), and 32 from the targets on whose waves fill the chip (2^18 7288 / 6870 /
 //   7049, FP64 6512 / 6393 / 6713; 200001 6036 / 6223 / -, FP64 5520 / 5812 / -).
+// - Short lists and short rays (scenes of at most 32^3 cells, us with 8 / 16 / 32 /
+//   64): the march of a tile is then short beside its walk, so larger tiles, and
+//   the total decides, not the largest scene.  64 sources on 16^3 cells, 64 scenes
+//   of 4096 targets 300 / 267 / 265 / 264, 64 of 16384 952 / 812 / 768 / 705; on
+//   32^3 1439 / 1283 / 1230 / 1266, FP64 1470 / 1288 / 1203 / 1171; 256 sources
+//   2576 / 2324 / 2266 / 2360, FP64 2610 / 2349 / 2270 / 2222; 64 scenes of 4096
+//   targets of 256 sources 756 / 724 / 731 / 732.
 inline int tile_from_size(const BatchSize &b)
 {
     const int64_t k16 = (int64_t)1 << 16;
     const bool few = b.max_src < 4096, lists = long_lists(b);
     const int64_t small_t = b.max_src < 1024 ? k16 / 2 : few ? k16 : 2 * k16;
     const int64_t mid_t = few || b.fp64 ? 4 * k16 : 7 * k16;
+    const bool short_rays = b.grid <= 32;
     int h = 1;
-    if (b.max_t <= small_t && b.total <= 8 * k16)
+    if (short_rays && b.max_src < 256 && b.total >= k16)
+        h = b.total < 4 * k16 ? 16 : b.grid <= 16 || b.fp64 ? 64 : 32;
+    else if (short_rays && b.max_src < 1024 && b.total >= 8 * k16)
+        h = b.fp64 || b.total >= 64 * k16 ? 64 : 32;
+    else if (b.max_t <= small_t && b.total <= 8 * k16)
         while (h < 8 && (int64_t)h * 2 * 4096 <= b.total) h *= 2;
     else if (b.max_t <= mid_t && b.total < 64 * k16)
         h = b.total < 32 * k16 ? 16 : 32;
@@ -81,10 +94,12 @@ inline int size_class(int64_t v)
 }
 
 // The autotuner's size class of a batch: all that the choice above is made from.
-using TileClass = std::array<int, 5>;
+using TileClass = std::array<int, 6>;
 inline TileClass tile_class(const BatchSize &b)
 {
-    return {size_class(b.total), size_class(b.max_src), size_class(b.max_t), b.fp64 ? 1 : 0, long_lists(b) ? 1 : 0};
+    const int grid = size_class(b.grid);
+    return {size_class(b.total), size_class(b.max_src), size_class(b.max_t), grid < 4 ? 4 : grid > 6 ? 6 : grid,
+            b.fp64 ? 1 : 0, long_lists(b) ? 1 : 0};
 }
 
 }  // namespace start

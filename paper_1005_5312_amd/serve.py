@@ -177,9 +177,9 @@ class GpuExecutor(Executor):
 
     Without autotune the library picks the tile size from the call's size.
     With autotune, the first batch of each size class (total targets, largest
-    item's targets and largest source count, each rounded up to a power of
-    two, any FP64 item, every opening angle below 0.4) up to 2^17 targets on a
-    slot is run through start_autotune_rates, which computes it with several
+    item's targets, largest source count and largest grid, each rounded up to
+    a power of two, any FP64 item, every opening angle below 0.4) up to 2^17
+    targets on a slot is run through start_autotune_rates, which computes it with several
     tile sizes and keeps the fastest for that class; later
     batches of the class use it (results do not depend on it).  This tunes on
     the request path, so the first batch of a class is slow."""
@@ -294,7 +294,8 @@ class GpuExecutor(Executor):
             if items:
                 total = sum(batch[k].n_t for k in batched)
                 n_src = max(batch[k].scene.n_src for k in batched)
-                key = (*(max(0, (v - 1).bit_length()) for v in (total, max(batch[k].n_t for k in batched), n_src)),
+                key = (*(max(0, (v - 1).bit_length()) for v in (total, max(batch[k].n_t for k in batched), n_src,
+                                                                max(it["grid"].G for it in items))),
                        any(batch[k].prec == "fp64" for k in batched), all(batch[k].theta < 0.4 for k in batched))
                 if self.autotune and key[0] <= self.TUNE_MAX_CLASS and key not in self.tuned[slot]:
                     ctx.autotune_rates(items, reps=2)

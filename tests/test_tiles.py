@@ -17,7 +17,7 @@ int main(int argc, char **argv)
 {
     start::BatchSize b;
     b.total = atoll(argv[1]), b.max_t = atoll(argv[2]), b.max_src = atoll(argv[3]);
-    b.theta = atof(argv[4]), b.fp64 = atoi(argv[5]) != 0;
+    b.theta = atof(argv[4]), b.fp64 = atoi(argv[5]) != 0, b.grid = atoi(argv[6]);
     printf("%d", start::tile_from_size(b));
     for (int v : start::tile_class(b)) printf(" %d", v);
     printf("\n");
@@ -36,9 +36,9 @@ def choose(tmp_path_factory):
     except FileNotFoundError:
         pytest.skip("no host C++ compiler")
 
-    def run(n, n_src, theta=1.0, prec="fp32c", max_t=None):
-        out = subprocess.run([str(d / "t"), *map(str, (n, max_t or n, n_src, theta, int(prec == "fp64")))], check=True,
-                             capture_output=True, text=True).stdout.split()
+    def run(n, n_src, theta=1.0, prec="fp32c", max_t=None, grid=128):
+        args = map(str, (n, max_t or n, n_src, theta, int(prec == "fp64"), grid))
+        out = subprocess.run([str(d / "t"), *args], check=True, capture_output=True, text=True).stdout.split()
         return int(out[0]), tuple(map(int, out[1:]))
     return run
 
@@ -74,10 +74,19 @@ def test_scenes_of_a_batch(choose):
     assert choose(64 * K, 16384, max_t=16384)[0] == 64
 
 
+@pytest.mark.parametrize("n,n_src,grid,prec,tile", [
+    # short lists on small grids: the total decides
+    (K - 1, 64, 16, "fp32c", 8), (K, 64, 16, "fp32c", 16), (4 * K, 64, 16, "fp32c", 64), (4 * K, 64, 32, "fp32c", 32),
+    (4 * K, 64, 32, "fp64", 64), (4 * K, 64, 64, "fp64", 8), (4 * K, 256, 32, "fp32c", 8), (8 * K, 256, 32, "fp32c", 32),
+    (8 * K, 1023, 32, "fp64", 64), (8 * K, 1024, 32, "fp64", 8), (64 * K, 256, 32, "fp32c", 64)])
+def test_scenes_with_few_sources(choose, n, n_src, grid, prec, tile):
+    assert choose(n, n_src, prec=prec, max_t=4096, grid=grid)[0] == tile
+
+
 def test_size_classes_tell_the_choices_apart(choose):
     """A batch of many small FP32C scenes and one large FP64 call of the same total
     and sources have tiles of their own."""
-    base = dict(n=16 * K, n_src=1024, theta=0.5, prec="fp32c")
+    base = dict(n=16 * K, n_src=1024, theta=0.5, prec="fp32c")   # on 128^3 cells
     cls = choose(**base)[1]
-    for other in (dict(prec="fp64"), dict(theta=0.3), dict(max_t=4096), dict(n=32 * K), dict(n_src=64)):
+    for other in (dict(prec="fp64"), dict(theta=0.3), dict(max_t=4096), dict(n=32 * K), dict(n_src=64), dict(grid=32)):
         assert choose(**{**base, **other})[1] != cls, other
