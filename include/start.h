@@ -277,10 +277,10 @@ start_status start_set_tile_targets(start_ctx *ctx, int tile_targets);
  * the batch's size class in the context's table: total targets, largest
  * item's targets, largest source count and largest grid (16^3 and smaller,
  * 32^3, larger), each rounded up to a power of two, any FP64 item or none, and
- * whether every opening angle is below 0.4 with 256 to 4095 sources.  The size it would take by itself is kept unless
- * another is at least 3% faster.  best_tile
- * and best_ms (host, may be NULL) receive the choice and its mean time.
- * Synchronous. */
+ * whether every opening angle is below 0.4 (or all are 0) with 256 to 4095
+ * sources.  The size it would take by itself is kept unless another is at
+ * least 3% faster.  best_tile and best_ms (host, may be NULL) receive the
+ * choice and its mean time.  Synchronous. */
 start_status start_autotune_rates(start_ctx *ctx, int n_items, const start_item *items, int reps, int *best_tile,
                                   double *best_ms);
 

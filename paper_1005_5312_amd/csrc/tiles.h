@@ -51,8 +51,12 @@ inline bool long_lists(const BatchSize &b) { return b.theta < 0.4 && b.max_src >
 // - Long lists (256 sources or more, theta below 0.4) in FP32C: 64 from 3 * 2^17
 //   targets (1024 sources at 0.3: 330001 27144 / 23934 / 24612, 420001 33498 /
 //   28629 / 27819, 2^20 - / 57570 / 53620; 64 sources, 2^19: 3650 / 3840 with 32 /
-//   64), and 32 from the targets on whose waves fill the chip (2^18 7288 / 6870 /
-//   7049, FP64 6512 / 6393 / 6713; 200001 6036 / 6223 / -, FP64 5520 / 5812 / -).
+//   64; 256 at 0.2: 420001 14673 / 13172 / 14017, 2^19 17771 / 16051 / 15698, so
+//   up to 512 sources from 2^19), and 32 from the targets on whose waves fill the
+//   chip (2^18 7288 / 6870 / 7049, FP64 6512 / 6393 / 6713; 200001 6036 / 6223 / -,
+//   FP64 5520 / 5812 / -), but 16 there at theta = 0 (1024 sources 13529 / 14156 /
+//   15624, FP64 13058 / 13870 / 14775) and beyond 2048 sources (3000 at 0.35: 9226 /
+//   9379 / 9978, FP64 8388 / 8769 / 9756).
 // - Short lists and short rays (scenes of at most 32^3 cells, us with 8 / 16 / 32 /
 //   64): the march of a tile is then short beside its walk, so larger tiles, and
 //   the total decides, not the largest scene.  64 sources on 16^3 cells, 64 scenes
@@ -79,8 +83,8 @@ inline int tile_from_size(const BatchSize &b)
     else if (few && b.fp64)
         h = 64;
     else
-        h = b.total < (lists ? 6 * k16 : b.fp64 ? 16 * k16 : 24 * k16) ? 32 : 64;
-    if (lists && h == 16 && b.total >= 7 * k16 / 2) h = 32;
+        h = b.total < (lists ? (b.max_src > 512 ? 6 : 8) * k16 : b.fp64 ? 16 * k16 : 24 * k16) ? 32 : 64;
+    if (lists && b.theta > 0.0 && b.max_src <= 2048 && h == 16 && b.total >= 7 * k16 / 2) h = 32;
     while (h < 64 && h * b.max_src < 64) h *= 2;
     return h;
 }
@@ -99,7 +103,7 @@ inline TileClass tile_class(const BatchSize &b)
 {
     const int grid = size_class(b.grid);
     return {size_class(b.total), size_class(b.max_src), size_class(b.max_t), grid < 4 ? 4 : grid > 6 ? 6 : grid,
-            b.fp64 ? 1 : 0, long_lists(b) ? 1 : 0};
+            b.fp64 ? 1 : 0, long_lists(b) ? (b.theta > 0.0 ? 1 : 2) : 0};
 }
 
 }  // namespace start

@@ -68,6 +68,16 @@ def test_choice(choose, n, n_src, theta, prec, tile):
     assert choose(n, n_src or n, theta, prec)[0] == tile
 
 
+@pytest.mark.parametrize("n,n_src,theta,prec,tile", [
+    # the smallest opening angle, and the ends of the range of sources
+    (4 * K, 1024, 0.0, "fp32c", 16), (4 * K, 1024, 0.0, "fp64", 16), (4 * K, 1024, 0.1, "fp32c", 32),
+    (4 * K, 2048, 0.2, "fp32c", 32), (4 * K, 2049, 0.2, "fp32c", 16), (4 * K, 3000, 0.2, "fp64", 16),
+    (7 * K, 512, 0.2, "fp32c", 32), (7 * K, 513, 0.2, "fp32c", 64), (8 * K, 512, 0.2, "fp32c", 64),
+    (8 * K, 512, 0.0, "fp32c", 64)])
+def test_long_lists(choose, n, n_src, theta, prec, tile):
+    assert choose(n, n_src, theta, prec)[0] == tile
+
+
 def test_scenes_of_a_batch(choose):
     assert choose(4 * K, 16384, max_t=16384)[0] == 8
     assert choose(16 * K, 16384, max_t=16384)[0] == 16
@@ -88,5 +98,6 @@ def test_size_classes_tell_the_choices_apart(choose):
     and sources have tiles of their own."""
     base = dict(n=16 * K, n_src=1024, theta=0.5, prec="fp32c")   # on 128^3 cells
     cls = choose(**base)[1]
+    assert choose(**{**base, "theta": 0.0})[1] != choose(**{**base, "theta": 0.3})[1]
     for other in (dict(prec="fp64"), dict(theta=0.3), dict(max_t=4096), dict(n=32 * K), dict(n_src=64), dict(grid=32)):
         assert choose(**{**base, **other})[1] != cls, other
