@@ -371,7 +371,7 @@ def batch_bench(n_inst=256, n_p=1 << 14, seed=9, reps=3):
                           "batched_evals_per_s": n_total / t_batched_tuned,
                           "single_tile_targets": best_single, "one_call_each_ms": t_single_tuned * 1e3,
                           "one_call_each_evals_per_s": n_total / t_single_tuned},
-            "default_tiles": "from the call size: about total targets / 4096, a power of two in [1, 64]",
+            "default_tiles": "by targets, sources, grid, opening angle and precision (a power of two, at most 64)",
             "plan_replay": {"batched_ms": t_plan * 1e3, "one_instance_call_ms": t_one * 1e3,
                             "one_instance_plan_ms": t_one_plan * 1e3,
                             "what": "the batch (and one 2^14 instance) staged once and its rate kernels replayed "

@@ -762,7 +762,7 @@ start_status start_compute_rates_upstream(start_ctx *ctx, const start_tree *tree
     const size_t lb_bytes = Eb * upstream_link_bytes();
     char *links = (char *)alloc(2 * lb_bytes);
     unsigned *roots = (unsigned *)alloc(Eb * sizeof(unsigned));
-    unsigned *words = (unsigned *)alloc(256);   // [0] root count, [1] "more" flag
+    unsigned *words = (unsigned *)alloc(256);   // [0] root count
     const int64_t nslots = n;   // one neighbour count per particle
     unsigned *nbc = (unsigned *)alloc((size_t)(nslots + 1) * sizeof(unsigned));
     void *nb_scan_tmp = alloc(scan_temp_bytes(nslots + 1));

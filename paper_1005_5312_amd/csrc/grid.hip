@@ -234,8 +234,8 @@ __device__ inline unsigned pairs_before(uint2 c, int s)
 // listed particle, of which ~60% lie in the support), latency on small ones.
 // A thread per group looping over its rows by itself had 8 times fewer waves
 // (128 on a 32^3 grid, on 1024 SIMDs) and waited in each row for the lane with
-// the longest run: 195 us on 32^3, 239 on 64^3, 771 on 128^3; now 24, 88 and
-// 555 (alone).
+// the longest run: 195 us on 32^3, 239 on 64^3, 771 on 128^3; now 26, 87 and
+// 600 (alone).
 //
 // kGatherCount also counts the (centre, particle) pairs inside the support of
 // each centre and slice; kFillPairs records them with their weights, slice by

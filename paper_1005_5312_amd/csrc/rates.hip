@@ -1378,14 +1378,14 @@ int item_key_bits(int n_items)
 }
 
 // Morton bits of the targets' order, so that the whole key is a few digits of 8
-// bits: a pass of the sort takes ~13 us (two launches), or ~4 of the one launch
+// bits: a pass of the sort takes 12-14 us (two launches), or ~4 of the one launch
 // up to 8192 targets, and the order only has to bring together what a tile
 // marches.
 // Two digits up to 2^16 targets of at most 1024 sources, whose rays and walks
-// are few: a call on 16457 uniform targets of 64 sources takes 184 us with three
-// and 172 with two, on targets in clusters 134 and 124 (65536 of 1024 sources:
-// 631 and 609, in clusters 358 and 361).  Where all particles emit, clusters
-// need the third digit (65536 of them: 1440 us, 1541 with two).  Three up to
+// are few: a call on 16457 uniform targets of 64 sources takes 137 us with three
+// and 126 with two (65536 of 1024 sources: 22 us less with two, in clusters 3
+// more).  Where all particles emit, clusters need the third digit (65536 of
+// them: 1440 us, 1541 with two).  Three up to
 // 2^18 targets (64 cells a target there).  Four beyond, the item's number among
 // them as long as no item is larger than that.
 int morton_bits(const RateSpec *specs, int n, int64_t n_targets)

@@ -16,7 +16,7 @@
 //      and the index of the first node after its subtree (stackless walk);
 //   5. the virtual source of each cell, eqs. (14)-(15), is summed bottom-up in
 //      FP64, children in depth-first order: subtrees of at most 128 sources by
-//      one wave each in LDS, the cells above them by one block.
+//      one wave each in LDS, the cells above them level by level.
 // Below ~2^18 sources launches are what a build costs (~5 us each), so it has
 // as few as it can and waits for the device once, at its end: the node count
 // stays on the device until then and the kernels are launched for its bound 2n.

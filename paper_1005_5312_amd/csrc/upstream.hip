@@ -54,7 +54,9 @@ __device__ inline unsigned lanes_below(uint64_t m)
 // box), cut to the cells that the sphere of radius 2h reaches, and list the
 // rows' particles, the first of each row, the second, and so on, in LDS; the
 // listed ones are tested 64 at a time (a lane testing its own row's left most
-// lanes idle: 671 us for both passes over 2^18 particles, 433 so).  A ballot
+// lanes idle: 670 us for both passes over 2^18 particles, 431 so; 568 on the
+// clumpy medium, whose supports near the box's faces are up to 1.9 times the
+// mean).  A ballot
 // of the ones within 2h gives each its place, so the records come out in a
 // fixed order (row chunk, step, row).  FILL = false writes the count to
 // count[i]; FILL = true writes the records from nb_off[i] (the counts scanned).
